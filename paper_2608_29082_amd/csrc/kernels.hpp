@@ -1264,349 +1264,6 @@ __global__ __launch_bounds__(256) void k_fill0(long cnt, T* out) {
   if (t < cnt) out[t] = T(0);
 }
 
-// ------------------------------------------------------------------ coarse tail in LDS
-// Levels lt .. J-1 of one V-cycle for CPB right-hand-side columns per
-// workgroup, with every vector of those levels in LDS (the operators are read
-// from global memory and stay in L2).  Columns are independent, so
-// workgroups never synchronise with each other; inside a workgroup the sweeps
-// are separated by barriers.  LDS layout (units of C, column-minor:
-// element (i, c) of a vector at off + i * CPB + c): per tail level u and f,
-// plus four scratch vectors of the largest tail level.
-constexpr int kTailMaxLevels = 12;
-template <class C>
-struct TailLevel {
-  Lvl<C> L;
-  Xfer<C> P;                // n_l x n_{l+1} (levels below the coarsest)
-  Xfer<C> R;                // n_{l+1} x n_l
-  int off_u, off_f;
-};
-template <class C>
-struct TailArgs {
-  int nl;                   // number of tail levels (the last one is the coarsest)
-  TailLevel<C> lv[kTailMaxLevels];
-  int off_s, off_ya, off_yb, off_t;
-  int KB, KR, KP, nu_pre, nu_post, per;
-  const double* prm;        // flat parameters, row `per` per level, first tail level first
-  const double* Ainv;       // coarsest inverse (row-major)
-  int nJ;
-  int lt;                   // global index of the first tail level
-};
-
-// The tail's operators stay in global memory (L2-resident) while its vectors
-// live in LDS.  Rows of width 1 .. kTailW load all their slots' indices (and
-// values) at once, so a sweep costs one global round trip rather than one per
-// slot; slots past the width repeat slot 0 and are not summed (same sums, same
-// order, as the slot loop).
-constexpr int kTailW = 8;
-
-// One work-item's row of a tail level, held in registers for the sweeps of a
-// level visit when every row has its own work-item (n * CPB <= blockDim.x) and
-// the widths are 1 .. kTailW: the sweeps then read only LDS.
-template <class C, bool WG>
-struct TRow {
-  int ac[kTailW], gc[kTailW];
-  C av[kTailW], gw[WG ? kTailW : 1];
-  C dg, ida, idg;
-};
-template <int CPB, bool WG, class C>
-__device__ __forceinline__ bool tl_cacheable(const Lvl<C>& L) {
-  return L.n * CPB <= (int)blockDim.x && L.w >= 1 && L.w <= kTailW && L.wg >= 1 && L.wg <= kTailW;
-}
-template <int CPB, bool WG, class C>
-__device__ __forceinline__ void tl_load_row(const Lvl<C>& L, TRow<C, WG>& R) {
-  const int e = threadIdx.x;
-  if (e >= L.n * CPB) return;
-  const int i = e / CPB;
-  // per-column operators (one column per workgroup): the operator column of this workgroup's column
-  const int vs = L.vs, vb = vs ? vcol(L, (int)blockIdx.x) : 0;
-#pragma unroll
-  for (int k = 0; k < kTailW; ++k) {
-    const size_t o = (size_t)(k < L.w ? k : 0) * L.ld + i;
-    const size_t og = (size_t)(k < L.wg ? k : 0) * L.ld + i;
-    R.ac[k] = L.col[o];
-    R.av[k] = vs ? L.val[o * vs + vb] : L.val[o];
-    R.gc[k] = L.gcol[og];
-    if constexpr (WG) R.gw[k] = L.gval[og];
-  }
-  R.dg = vs ? L.diag[(size_t)i * vs + vb] : L.diag[i];
-  R.ida = vs ? L.invdiag[(size_t)i * vs + vb] : L.invdiag[i];
-  R.idg = L.invdeg[i];
-}
-
-template <int CPB, class C, bool WG>
-__device__ __forceinline__ void tl_resid(const Lvl<C>& L, const C* f, const C* u, int uz, int jacobi, C* out,
-                                         const TRow<C, WG>& rc, bool cached) {
-  if (cached) {   // the row in registers (one row per work-item)
-    const int e = threadIdx.x;
-    if (e < L.n * CPB) {
-      const int c = e % CPB;
-      C v = f[e];
-      if (!uz) {
-        C au = rc.dg * u[e];
-#pragma unroll
-        for (int k = 0; k < kTailW; ++k)
-          if (k < L.w) au += rc.av[k] * u[rc.ac[k] * CPB + c];
-        v -= au;
-      }
-      if (jacobi) v *= rc.ida;
-      out[e] = v;
-    }
-    __syncthreads();
-    return;
-  }
-  // per-column operators (one column per workgroup, CPB == 1): value (o) of the workgroup's column
-  const int vs = L.vs, vb = vs ? vcol(L, (int)blockIdx.x) : 0;
-  auto vi = [&](size_t o) { return vs ? o * vs + vb : o; };
-  for (int e = threadIdx.x; e < L.n * CPB; e += blockDim.x) {
-    const int i = e / CPB, c = e - i * CPB;
-    C v = f[e];
-    if (!uz) {
-      C au = L.diag[vi(i)] * u[e];
-      if (L.w >= 1 && L.w <= kTailW) {
-        int jj[kTailW];
-        C vv[kTailW];
-#pragma unroll
-        for (int k = 0; k < kTailW; ++k) {
-          const size_t o = (size_t)(k < L.w ? k : 0) * L.ld + i;
-          jj[k] = L.col[o];
-          vv[k] = L.val[vi(o)];
-        }
-#pragma unroll
-        for (int k = 0; k < kTailW; ++k)
-          if (k < L.w) au += vv[k] * u[jj[k] * CPB + c];
-      } else {
-        for (int k = 0; k < L.w; ++k)
-          au += L.val[vi((size_t)k * L.ld + i)] * u[L.col[(size_t)k * L.ld + i] * CPB + c];
-      }
-      v -= au;
-    }
-    if (jacobi) v *= L.invdiag[vi(i)];
-    out[e] = v;
-  }
-  __syncthreads();
-}
-
-// out = a (M yin) + c x   (mode 0)   |   out = (oz ? 0 : out) + scale (a (M yin) + c x)   (mode 1)
-template <int CPB, bool WG, class C>
-__device__ __forceinline__ void tl_hop(const Lvl<C>& L, const C* yin, C a, const C* x, C cc, C* out, int mode,
-                                       C scale, int oz, const TRow<C, WG>& rc, bool cached) {
-  if (cached) {   // the row in registers (one row per work-item)
-    const int e = threadIdx.x;
-    if (e < L.n * CPB) {
-      const int i = e / CPB, c = e - i * CPB;
-      C sm = C(0);
-#pragma unroll
-      for (int k = 0; k < kTailW; ++k) {
-        if (k >= L.wg) continue;
-        C v = yin[rc.gc[k] * CPB + c];
-        if constexpr (WG) v *= rc.gw[k];
-        if (rc.gc[k] != i) sm += v;
-      }
-      const C v = hop_value(a, rc.idg, sm, cc, x[e]);
-      out[e] = mode == 0 ? v : hop_update(oz ? C(0) : out[e], scale, v);
-    }
-    __syncthreads();
-    return;
-  }
-  for (int e = threadIdx.x; e < L.n * CPB; e += blockDim.x) {
-    const int i = e / CPB, c = e - i * CPB;
-    C sm = C(0);
-    if (L.wg >= 1 && L.wg <= kTailW) {
-      int jj[kTailW];
-      C ww[kTailW];
-#pragma unroll
-      for (int k = 0; k < kTailW; ++k) {
-        const size_t o = (size_t)(k < L.wg ? k : 0) * L.ld + i;
-        jj[k] = L.gcol[o];
-        if constexpr (WG) ww[k] = L.gval[o];
-      }
-#pragma unroll
-      for (int k = 0; k < kTailW; ++k) {
-        if (k >= L.wg) continue;
-        C v = yin[jj[k] * CPB + c];
-        if constexpr (WG) v *= ww[k];
-        if (jj[k] != i) sm += v;
-      }
-    } else {
-      for (int k = 0; k < L.wg; ++k) {
-        const int j = L.gcol[(size_t)k * L.ld + i];
-        C v = yin[j * CPB + c];
-        if constexpr (WG) v *= L.gval[(size_t)k * L.ld + i];
-        if (j != i) sm += v;
-      }
-    }
-    const C v = hop_value(a, L.invdeg[i], sm, cc, x[e]);
-    out[e] = mode == 0 ? v : hop_update(oz ? C(0) : out[e], scale, v);
-  }
-  __syncthreads();
-}
-
-// out = X v  for an ELL transfer X (rows X.n)
-template <int CPB, class C>
-__device__ __forceinline__ void tl_xfer(const Xfer<C>& X, const C* v, C* out, int add, C scale, int oz) {
-  for (int e = threadIdx.x; e < X.n * CPB; e += blockDim.x) {
-    const int i = e / CPB, c = e - i * CPB;
-    C acc = C(0);
-    if (X.w >= 1 && X.w <= kTailW) {
-      int jj[kTailW];
-      C ww[kTailW];
-#pragma unroll
-      for (int k = 0; k < kTailW; ++k) {
-        const size_t o = (size_t)(k < X.w ? k : 0) * X.n + i;
-        jj[k] = X.col[o];
-        ww[k] = X.val[o];
-      }
-#pragma unroll
-      for (int k = 0; k < kTailW; ++k)
-        if (k < X.w && ww[k] != C(0)) acc += ww[k] * v[jj[k] * CPB + c];
-    } else {
-      for (int k = 0; k < X.w; ++k) {
-        const C w = X.val[(size_t)k * X.n + i];
-        if (w != C(0)) acc += w * v[X.col[(size_t)k * X.n + i] * CPB + c];
-      }
-    }
-    out[e] = add ? (oz ? C(0) : out[e]) + scale * acc : scale * acc;
-  }
-  __syncthreads();
-}
-
-// u = (oz ? 0 : u) + scale * sum_k c_k M^k x  (Horner, as the per-level sweeps)
-template <int CPB, bool WG, class C>
-__device__ __forceinline__ void tl_conv_add(const Lvl<C>& L, const double* c, int K, const C* x, double scale, C* u,
-                                            int oz, C* ya, C* yb, const TRow<C, WG>& rc, bool cached) {
-  if (K == 0) {
-    const C a0 = (C)(scale * c[0]);
-    for (int e = threadIdx.x; e < L.n * CPB; e += blockDim.x) u[e] = (oz ? C(0) : u[e]) + a0 * x[e];
-    __syncthreads();
-    return;
-  }
-  const C* yin = x;
-  C a = (C)c[K];
-  C* buf[2] = {ya, yb};
-  int cur = 0;
-  for (int k = K - 1; k >= 1; --k) {
-    tl_hop<CPB, WG>(L, yin, a, x, (C)c[k], buf[cur], 0, C(0), 0, rc, cached);
-    yin = buf[cur];
-    cur ^= 1;
-    a = C(1);
-  }
-  tl_hop<CPB, WG>(L, yin, a, x, (C)c[0], u, 1, (C)scale, oz, rc, cached);
-}
-
-// the coarsest tail level: u = A^{-1} f (FP64 accumulation)
-template <int CPB, class C>
-__device__ __forceinline__ void tl_coarse(const TailArgs<C>& T, C* sm) {
-  const TailLevel<C>& tl = T.lv[T.nl - 1];
-  const C* f = sm + tl.off_f;
-  C* u = sm + tl.off_u;
-  // per-column operators (CPB == 1): the inverse of this workgroup's column
-  const Lvl<C>& LJ = tl.L;
-  const double* Ai = LJ.vs ? T.Ainv + (size_t)vcol(LJ, (int)blockIdx.x) * T.nJ * T.nJ : T.Ainv;
-  for (int e = threadIdx.x; e < T.nJ * CPB; e += blockDim.x) {
-    const int i = e / CPB, c = e - i * CPB;
-    double acc = 0.0;
-    for (int j = 0; j < T.nJ; ++j) acc += Ai[(size_t)i * T.nJ + j] * (double)f[j * CPB + c];
-    u[e] = (C)acc;
-  }
-  __syncthreads();
-}
-
-// One learnable cycle over tail levels q0 .. nl-1 in LDS: u_q0 <- LMG(f_q0, u_q0)
-// (uz0: u_q0 is logically zero on entry; deeper levels always start from zero).
-template <int CPB, bool WG, class C>
-__device__ __forceinline__ void tl_cycle(const TailArgs<C>& T, C* sm, int q0, int uz0) {
-  C *s = sm + T.off_s, *ya = sm + T.off_ya, *yb = sm + T.off_yb, *t = sm + T.off_t;
-  // down: pre-smoothing and restriction
-  for (int q = q0; q + 1 < T.nl; ++q) {
-    const TailLevel<C>& tl = T.lv[q];
-    const double* p = T.prm + (size_t)q * T.per;
-    const double *cB = p + 2, *cR = cB + T.KB + 1;
-    C* u = sm + tl.off_u;
-    const C* f = sm + tl.off_f;
-    TRow<C, WG> rc;
-    const bool cached = tl_cacheable<CPB, WG>(tl.L);
-    if (cached) tl_load_row<CPB, WG>(tl.L, rc);
-    int uz = q == q0 ? uz0 : 1;
-    for (int j = 0; j < T.nu_pre; ++j) {
-      tl_resid<CPB>(tl.L, f, u, uz, 1, s, rc, cached);
-      tl_conv_add<CPB, WG>(tl.L, cB, T.KB, s, p[1] * p[0], u, uz, ya, yb, rc, cached);
-      uz = 0;
-    }
-    // r = f - A u (u may still be zero when nu_pre == 0), then y = Phi_R r, f_{l+1} = R y
-    tl_resid<CPB>(tl.L, f, u, uz, 0, t, rc, cached);
-    if (uz) {  // u is logically zero: materialise it for the prolongation's update
-      for (int e = threadIdx.x; e < tl.L.n * CPB; e += blockDim.x) u[e] = C(0);
-      __syncthreads();
-    }
-    tl_conv_add<CPB, WG>(tl.L, cR, T.KR, t, 1.0, s, 1, ya, yb, rc, cached);
-    tl_xfer<CPB>(tl.R, s, sm + T.lv[q + 1].off_f, 0, C(1), 0);
-  }
-  tl_coarse<CPB>(T, sm);
-  // up: prolongation with Phi_P and post-smoothing
-  for (int q = T.nl - 2; q >= q0; --q) {
-    const TailLevel<C>& tl = T.lv[q];
-    const double* p = T.prm + (size_t)q * T.per;
-    const double *cB = p + 2, *cP = cB + T.KB + 1 + T.KR + 1;
-    C* u = sm + tl.off_u;
-    const C* f = sm + tl.off_f;
-    TRow<C, WG> rc;
-    const bool cached = tl_cacheable<CPB, WG>(tl.L);
-    if (cached) tl_load_row<CPB, WG>(tl.L, rc);
-    tl_xfer<CPB>(tl.P, sm + T.lv[q + 1].off_u, t, 0, C(1), 0);
-    tl_conv_add<CPB, WG>(tl.L, cP, T.KP, t, 1.0, u, 0, ya, yb, rc, cached);
-    for (int j = 0; j < T.nu_post; ++j) {
-      tl_resid<CPB>(tl.L, f, u, 0, 1, s, rc, cached);
-      tl_conv_add<CPB, WG>(tl.L, cB, T.KB, s, p[1] * p[0], u, 0, ya, yb, rc, cached);
-    }
-  }
-}
-
-// fmg == 0: e = LMG(A_lt, f, 0) over the tail levels lt .. J-1.
-// fmg == 1: e = FMG(f) over the same levels: f_{q+1} = R Phi_R(f_q), exact
-//           coarsest solve, then per level u_q = Phi_P(P u_{q+1}) and one cycle.
-template <int CPB, bool WG, class C, class TU>
-__global__ __launch_bounds__(1024) void k_tail(TailArgs<C> T, int B, const TU* __restrict__ fg,
-                                               TU* __restrict__ eg, int fmg) {
-  extern __shared__ __align__(16) unsigned char tail_smem[];
-  C* sm = reinterpret_cast<C*>(tail_smem);
-  const int col0 = blockIdx.x * CPB;
-  // load the first tail level's right-hand side for this workgroup's columns
-  {
-    const TailLevel<C>& t0 = T.lv[0];
-    for (int e = threadIdx.x; e < t0.L.n * CPB; e += blockDim.x) {
-      const int i = e / CPB, c = e - i * CPB;
-      sm[t0.off_f + e] = (col0 + c < B) ? (C)fg[(size_t)i * B + col0 + c] : C(0);
-    }
-    __syncthreads();
-  }
-  if (!fmg) {
-    tl_cycle<CPB, WG>(T, sm, 0, 1);
-  } else {
-    C *s = sm + T.off_s, *ya = sm + T.off_ya, *yb = sm + T.off_yb, *t = sm + T.off_t;
-    for (int q = 0; q + 1 < T.nl; ++q) {
-      const TailLevel<C>& tl = T.lv[q];
-      const double* cR = T.prm + (size_t)q * T.per + 2 + T.KB + 1;
-      tl_conv_add<CPB, WG>(tl.L, cR, T.KR, sm + tl.off_f, 1.0, s, 1, ya, yb, TRow<C, WG>{}, false);
-      tl_xfer<CPB>(tl.R, s, sm + T.lv[q + 1].off_f, 0, C(1), 0);
-    }
-    tl_coarse<CPB>(T, sm);
-    for (int q = T.nl - 2; q >= 0; --q) {
-      const TailLevel<C>& tl = T.lv[q];
-      const double* cP = T.prm + (size_t)q * T.per + 2 + T.KB + 1 + T.KR + 1;
-      tl_xfer<CPB>(tl.P, sm + T.lv[q + 1].off_u, t, 0, C(1), 0);
-      tl_conv_add<CPB, WG>(tl.L, cP, T.KP, t, 1.0, sm + tl.off_u, 1, ya, yb, TRow<C, WG>{}, false);
-      tl_cycle<CPB, WG>(T, sm, q, 0);
-    }
-  }
-  {
-    const TailLevel<C>& t0 = T.lv[0];
-    for (int e = threadIdx.x; e < t0.L.n * CPB; e += blockDim.x) {
-      const int i = e / CPB, c = e - i * CPB;
-      if (col0 + c < B) put(eg + (size_t)i * B + col0 + c, sm[t0.off_u + e]);
-    }
-  }
-}
-
 // ------------------------------------------------------------------ adjoint sweeps
 // Block-wide FP64 sum, written to part[blockIdx.x] (deterministic tree).
 __device__ __forceinline__ void block_sum_store(double v, double* part, double* red) {

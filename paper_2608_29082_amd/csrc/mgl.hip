@@ -25,6 +25,7 @@
 #include "krylov.hpp"
 #include "mgl.h"
 #include "plan.hpp"
+#include "tail.hpp"
 #include "tiles.hpp"
 
 using namespace mgl;
@@ -242,6 +243,7 @@ struct Engine final : EngineBase {
   size_t tile_mem_bytes = 0;
   // coarse tail (levels tail_lt .. J-1 in LDS, one workgroup per column)
   int tail_lt = -1;                 // shallowest level whose tail fits in LDS
+  int tail_own = -1;                // first of its levels that have no fused-convolution tiles
   std::vector<TailArgs<C>> tails;   // launch arguments for start levels tail_lt .. J-2
   std::vector<size_t> tail_bytes;
   char* wsbase = nullptr;
@@ -598,9 +600,50 @@ struct Engine final : EngineBase {
     return MG_OK;
   }
 
-  // Choose the shallowest start level without fused-convolution tiles whose
-  // coarse tail fits the workgroup's LDS, and prepare the launch arguments
-  // for every start level below it.
+  // slots that the rows of level l use in A and in the graph (padding slots, column == row, are last)
+  int used_slots(int l) const {
+    const HLevel& H = pl.lv[l];
+    int w = 1;
+    for (const HEll* e : {&H.off, H.graph_is_A ? &H.off : &H.graph})
+      for (int k = e->w - 1; k >= w; --k) {
+        const int* c = e->col.data() + (size_t)k * e->ld;
+        bool any = false;
+        for (int i = 0; i < H.n && !any; ++i) any = c[i] != i;
+        if (any) w = std::max(w, k + 1);
+      }
+    return w;
+  }
+  // LDS layout of the tail from level lt; returns its size in bytes
+  size_t tail_layout(int lt, TailArgs<C>& t) const {
+    auto r4 = [](long x) { return (x + 3) / 4 * 4; };
+    auto r16 = [](size_t b) { return (b + 15) & ~size_t(15); };
+    const int J = pl.J;
+    t.nl = J - lt;
+    t.nJ = pl.lv[J - 1].n;
+    t.inv_lds = t.nJ <= kTailInv;
+    long off = 0;
+    size_t work = 0;
+    for (int q = 0; q < t.nl; ++q) {
+      const int l = lt + q, n = pl.lv[l].n, rpt = t.lv[q].rpt;
+      t.lv[q].off_u = (int)off; off += r4(n);
+      t.lv[q].off_f = (int)off; off += r4(n);
+      if (l < J - 1) work = std::max(work, rpt ? 3 * (size_t)tail_stride(rpt, n, sizeof(C)) : 4 * r4(n) * sizeof(C));
+    }
+    t.off_prm = 0;
+    t.off_inv = (int)r16((size_t)(t.nl - 1) * per() * sizeof(C));
+    t.off_wk = t.off_inv + (int)r16(t.inv_lds ? (size_t)t.nJ * t.nJ * sizeof(double) : 0);
+    t.off_vec = t.off_wk + (int)r16(work);
+    return (size_t)t.off_vec + (size_t)off * sizeof(C);
+  }
+  // Choose the shallowest start level of the coarse tail and prepare the launch arguments for every
+  // start level from it down.
+  //  - Levels without fused-convolution tiles join while their vectors (two per level, four of the
+  //    largest) fit the workgroup's LDS; with 65 x 65 unknowns and one column the whole cycle is
+  //    then one launch.
+  //  - Where the cycle's vectors are not rounded to BF16, one tiled level of at most 4096 rows above
+  //    them joins too, unless it is the finest: its 12 launches (two smoothing steps on each side, the
+  //    transfers) take ~75 us whatever the batch, the tail's visit of 63 x 63 rows 15-20 us.  It sums its
+  //    residuals in the order of the per-level sweeps (TailArgs::nord), so no bit of the cycle changes.
   mg_status setup_tail() {
     tail_lt = -1;
     tails.clear();
@@ -611,51 +654,65 @@ struct Engine final : EngineBase {
     HIP_TRY(hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
     const int J = pl.J;
     auto r4 = [](long x) { return (x + 3) / 4 * 4; };
-    auto bytes_from = [&](int lt) {
-      long elems = 4 * r4(pl.lv[lt].n);
-      for (int l = lt; l < J; ++l) elems += 2 * r4(pl.lv[l].n);
-      return (size_t)elems * sizeof(C);
+    TailArgs<C> proto{};
+    std::vector<int> rpt(J, 0), wu(J, 0);
+    auto variant = [&](int l) {
+      const int n = pl.lv[l].n;
+      wu[l] = used_slots(l);
+      rpt[l] = (n + kTailThreads - 1) / kTailThreads;
+      if (rpt[l] > tail_max_rpt<C>() || wu[l] > kTailW || d[l].L.w < 1 || d[l].L.wg < 1) rpt[l] = 0;
+      if (d[l].L.gcol != d[l].L.col) wu[l] = kTailW + 1;
     };
-    // levels with fused-convolution tiles keep their per-level launches
-    for (int lt = 0; lt <= J - 2; ++lt)
-      if (J - lt <= kTailMaxLevels && bytes_from(lt) <= (size_t)maxlds && d[lt].td.ntiles == 0) {
-        tail_lt = lt;
-        break;
+    auto fits = [&](int lt) {
+      if (lt < 0 || J - lt > kTailMaxLevels) return false;
+      long old = 4 * r4(pl.lv[lt].n);
+      for (int l = lt; l < J; ++l) {
+        old += 2 * r4(pl.lv[l].n);
+        if (l < J - 1 && !wu[l]) variant(l);
       }
-    if (tail_lt < 0) return MG_OK;
-    const void* tail_fn = wgt() ? reinterpret_cast<const void*>(&k_tail<1, true, C, TU>)
-                                : reinterpret_cast<const void*>(&k_tail<1, false, C, TU>);
-    if (bytes_from(tail_lt) > 65536 &&
-        hipFuncSetAttribute(tail_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes_from(tail_lt)) !=
-            hipSuccess) {
+      TailArgs<C> t = proto;
+      for (int l = lt; l < J - 1; ++l) t.lv[l - lt].rpt = rpt[l];
+      return (d[lt].td.ntiles || (size_t)old * sizeof(C) <= (size_t)maxlds) && tail_layout(lt, t) <= (size_t)maxlds;
+    };
+    int lt = J - 1;
+    while (lt > 0 && d[lt - 1].td.ntiles == 0 && pl.lv[lt - 1].n <= 65536 && fits(lt - 1)) --lt;
+    tail_own = lt;
+    if (std::is_same<TH, TU>::value && pl.KR >= 1 && lt > 1 && lt < J && d[lt - 1].td.ntiles && fits(lt - 1) &&
+        rpt[lt - 1] != 0)
+      --lt;
+    if (lt > J - 2) return MG_OK;
+    TailArgs<C> top = proto;
+    for (int l = lt; l < J - 1; ++l) top.lv[l - lt].rpt = rpt[l];
+    const size_t most = tail_layout(lt, top);
+    const void* tail_fn = wgt() ? reinterpret_cast<const void*>(&k_tail<true, C>)
+                                : reinterpret_cast<const void*>(&k_tail<false, C>);
+    if (most > 65536 &&
+        hipFuncSetAttribute(tail_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess) {
       (void)hipGetLastError();
-      tail_lt = -1;   // large dynamic LDS unavailable: keep the per-level sweeps
-      return MG_OK;
+      return MG_OK;   // large dynamic LDS unavailable: keep the per-level sweeps
     }
-    for (int lt = tail_lt; lt <= J - 2; ++lt) {
+    tail_lt = lt;
+    for (; lt <= J - 2; ++lt) {
       TailArgs<C> t{};
-      t.nl = J - lt;
-      long off = 0;
-      for (int q = 0; q < t.nl; ++q) {
-        const int l = lt + q;
-        t.lv[q].L = d[l].L;
-        if (l < J - 1) { t.lv[q].P = d[l].P; t.lv[q].R = d[l].R; }
-        t.lv[q].off_u = (int)off; off += r4(pl.lv[l].n);
-        t.lv[q].off_f = (int)off; off += r4(pl.lv[l].n);
+      for (int l = lt; l < J; ++l) {
+        TailLevel<C>& v = t.lv[l - lt];
+        v.L = d[l].L;
+        if (l < J - 1) {
+          v.P = d[l].P;
+          v.R = d[l].R;
+          v.rpt = rpt[l];
+          v.w = wu[l];
+        }
       }
-      const long ns = r4(pl.lv[lt].n);
-      t.off_s = (int)off; off += ns;
-      t.off_ya = (int)off; off += ns;
-      t.off_yb = (int)off; off += ns;
-      t.off_t = (int)off; off += ns;
+      const size_t bytes = tail_layout(lt, t);
       t.KB = pl.KB; t.KR = pl.KR; t.KP = pl.KP;
       t.nu_pre = pl.nu_pre; t.nu_post = pl.nu_post; t.per = per();
       t.prm = dprm + (size_t)lt * per();
       t.Ainv = Ainv;
-      t.nJ = pl.lv[J - 1].n;
       t.lt = lt;
+      t.nord = std::max(0, tail_own - lt);
       tails.push_back(t);
-      tail_bytes.push_back(bytes_from(lt));
+      tail_bytes.push_back(bytes);
     }
     return MG_OK;
   }
@@ -834,11 +891,29 @@ struct Engine final : EngineBase {
     }
   }
 
-  // e = LMG(A_l, f, 0) (fmg: e = FMG(f)) for levels l .. J-1 in one launch (l >= tail_lt)
-  mg_status run_tail(int l, const TU* f, TU* e, hipStream_t st, int fmg = 0) {
+  // whether levels l .. J-1 run as one launch of the tail.  A cycle that starts from a nonzero
+  // iterate or records a checkpoint does so only where the tail gives the bits of the per-level
+  // sweeps it stands for: not with BF16 intermediates (the tail keeps them in FP32), nor with K_R = 0
+  // (the restriction then scales after its sum).
+  bool in_tail(int l, int uz, bool ck) const {
+    if (tail_lt < 0 || l < tail_lt || l >= pl.J - 1) return false;
+    return (uz && !ck) || (std::is_same<TH, TU>::value && pl.KR >= 1);
+  }
+  // e = LMG(A_l, f, e) (uz: e is zero on entry; fmg: e = FMG(f)) for levels l .. J-1 in one launch;
+  // with ck, the levels below l are recorded there
+  mg_status run_tail(int l, const TU* f, TU* e, hipStream_t st, int uz = 1, const Ck* ck = nullptr, int fmg = 0) {
     const int q = l - tail_lt;
-    WG_SPLIT(hipLaunchKernelGGL((k_tail<1, WGv, C, TU>), dim3(B()), dim3(1024), tail_bytes[q], st, tails[q], B(),
-                                f, e, fmg));
+    TailArgs<C> t = tails[q];
+    if (!uz) t.nord = std::max(t.nord, 1);
+    if (ck) {
+      t.nord = t.nl;
+      for (int k = 1; k < t.nl; ++k) {
+        t.ckf[k] = ck->f[l + k];
+        t.cku[k] = ck->u[l + k];
+      }
+    }
+    WG_SPLIT(hipLaunchKernelGGL((k_tail<WGv, C>), dim3(B()), dim3(kTailThreads), tail_bytes[q], st, t, B(), f, e, uz,
+                                fmg));
     LAUNCH_OK();
     return MG_OK;
   }
@@ -1042,7 +1117,7 @@ struct Engine final : EngineBase {
 
   // u = LMG(A_l, f, u) (Alg. 2); uz: u is identically zero on entry
   mg_status fwd(int l, const TU* f, TU* u, int uz, const Ck* ck, hipStream_t st) {
-    if (tail_lt >= 0 && l >= tail_lt && l < pl.J - 1 && uz && !ck) return run_tail(l, f, u, st);
+    if (in_tail(l, uz, ck != nullptr)) return run_tail(l, f, u, st, uz, ck);
     if (l == pl.J - 1) return coarse(f, u, 0, st);
     DL& D = d[l];
     for (int j = 0; j < pl.nu_pre; ++j) {
@@ -1331,7 +1406,7 @@ struct Engine final : EngineBase {
       fl = d[l + 1].f;
     }
     TU* ult = lt == 0 ? u0 : d[lt].u;
-    if (lt < J - 1) MG_TRY(run_tail(lt, fl, ult, st, 1));
+    if (lt < J - 1) MG_TRY(run_tail(lt, fl, ult, st, 1, nullptr, 1));
     else MG_TRY(coarse(fl, ult, 0, st));
     for (int l = lt - 1; l >= 0; --l) {
       const TU* f = l == 0 ? f0 : d[l].f;
