@@ -613,6 +613,390 @@ __global__ __launch_bounds__(MODE == 1 ? kGT : kGTH) void k_hz_gmres(CEll<T> A, 
   }
 }
 
+// ------------------------------------------------------------------ GMRES smoothing step, rows in registers
+// The same step for levels of at most 1536 rows with each work-item's rows (1 or
+// 3 of them, row r of work-item t being t + r * 512) in registers: A's rows, r,
+// d0, u and the basis vectors.  Only what neighbours read is in LDS: the vector a
+// sparse product gathers, in two buffers used in turn, so a product costs one
+// barrier and the Gram-Schmidt sweeps none.
+//
+// What bounds it: one workgroup per column walks 6 dependent products and 2 v
+// + 1 reductions, so the cost is latency.  The reductions dominated the sweep
+// form (lane exchanges through the LDS pipe, twelve per double and wavefront):
+// here up to eight sums are reduced together, each lane-exchange step halving
+// the values a lane carries (row operations and the gfx950 row swaps, no LDS),
+// one barrier per reduction (two buffers in turn), and every wavefront sums
+// the waves' totals by itself into scalars.  512 work-items, so that a
+// work-item has 256 registers.
+constexpr int kGR = 512;
+constexpr int kGRv = 4;          // GMRES steps of this form (at most)
+constexpr int kGRw = 8;          // slots per row (at most)
+
+template <int CTRL>
+__device__ __forceinline__ double hz_dpp(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double hz_pair(unsigned lo, unsigned hi) {
+  return __longlong_as_double(((long long)hi << 32) | lo);
+}
+// v + the value of the lane 16 (32) away, in both
+__device__ __forceinline__ double hz_add16(double v) {
+  const long long b = __double_as_longlong(v);
+  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+  return hz_pair(l[0], h[0]) + hz_pair(l[1], h[1]);
+}
+__device__ __forceinline__ double hz_add32(double v) {
+  const long long b = __double_as_longlong(v);
+  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+  return hz_pair(l[0], h[0]) + hz_pair(l[1], h[1]);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppRor4 = 0x124, kDppRor8 = 0x128, kDppHalfMirror = 0x141;
+__device__ __forceinline__ double hz_lane(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Sums over the workgroup (8 wavefronts) of NV values per work-item (NV = 1, 3,
+// 5, 7 or 9: dot products and, last, a norm), in a fixed order, the totals
+// uniform in every work-item.  red: 8 x 9 doubles, another buffer for every
+// second call (one barrier inside; the next call's writes then never meet this
+// one's reads).
+template <int NV>
+__device__ __forceinline__ void hz_group_sum(double (&a)[9], double* red) {
+  const int ln = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  double x;                       // lane l: the wavefront's sum of value l & 7 (of the first NV - 1)
+  const bool b0 = ln & 1, b1 = ln & 2, b2 = ln & 4;
+  if constexpr (NV > 1) {
+    double p[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const double lo = 2 * k < NV - 1 ? a[2 * k] : 0.0, hi = 2 * k + 1 < NV - 1 ? a[2 * k + 1] : 0.0;
+      p[k] = (b0 ? hi : lo) + hz_dpp<kDppXor1>(b0 ? lo : hi);
+    }
+    const double q0 = (b1 ? p[1] : p[0]) + hz_dpp<kDppXor2>(b1 ? p[0] : p[1]);
+    const double q1 = (b1 ? p[3] : p[2]) + hz_dpp<kDppXor2>(b1 ? p[2] : p[3]);
+    x = (b2 ? q1 : q0) + hz_dpp<kDppRor4>(b2 ? q0 : q1);
+    x += hz_dpp<kDppRor8>(x);
+    x = hz_add32(hz_add16(x));
+  }
+  double y = a[NV - 1];
+  y += hz_dpp<kDppXor1>(y);
+  y += hz_dpp<kDppXor2>(y);
+  y += hz_dpp<kDppHalfMirror>(y);
+  y += hz_dpp<kDppRor8>(y);
+  y = hz_add32(hz_add16(y));
+  if (NV > 1 && ln < 8) red[wv * 9 + ln] = x;
+  if (ln == 8) red[wv * 9 + 8] = y;
+  __syncthreads();
+  if constexpr (NV > 1) {
+    x = red[(ln >> 3) * 9 + (ln & 7)];
+    x += hz_dpp<kDppRor8>(x);
+    x = hz_add32(hz_add16(x));
+#pragma unroll
+    for (int k = 0; k < NV - 1; ++k) a[k] = hz_lane(x, k);
+  }
+  y = red[(ln & 7) * 9 + 8];
+  y += hz_dpp<kDppXor1>(y);
+  y += hz_dpp<kDppXor2>(y);
+  y += hz_dpp<kDppHalfMirror>(y);
+  a[NV - 1] = hz_lane(y, 0);
+}
+
+// Least squares min || beta e_1 - H y || of an (m + 1) x m Hessenberg matrix with
+// a real subdiagonal (m <= kGRv), as hz_givens_lsq, in registers: complex
+// Givens rotations [c s; -conj(s) c], then back substitution; y_t scaled by sc[t].
+__device__ __forceinline__ void hz_lsq_r(const double2* Hs, int m, double beta, const double (&sc)[kGRv + 1],
+                                         double2* yls) {
+  double2 H[kGRv + 1][kGRv], g[kGRv + 1], sn[kGRv], y[kGRv];
+  double cs[kGRv];
+#pragma unroll
+  for (int t = 0; t <= kGRv; ++t) {
+    g[t] = zc(t == 0 ? beta : 0.0, 0.0);
+#pragma unroll
+    for (int j = 0; j < kGRv; ++j)
+      if (t <= j + 1) H[t][j] = Hs[t * kGRv + j];
+  }
+#pragma unroll
+  for (int j = 0; j < kGRv; ++j) {
+#pragma unroll
+    for (int k = 0; k < j; ++k) {
+      const double2 a = H[k][j], bb = H[k + 1][j], sb = zmul(sn[k], bb), ca = zmul(zconj(sn[k]), a);
+      H[k][j] = zc(cs[k] * a.x + sb.x, cs[k] * a.y + sb.y);
+      H[k + 1][j] = zc(cs[k] * bb.x - ca.x, cs[k] * bb.y - ca.y);
+    }
+    const double2 a = H[j][j];
+    const double hb = H[j + 1][j].x, na2 = a.x * a.x + a.y * a.y, na = sqrt(na2), d = sqrt(na2 + hb * hb);
+    const double q = hb / (na * d);
+    cs[j] = d == 0.0 ? 1.0 : na / d;
+    sn[j] = d == 0.0 ? zc(0.0, 0.0) : (na == 0.0 ? zc(1.0, 0.0) : zc(a.x * q, a.y * q));
+    const double sr = sn[j].x * hb, si = sn[j].y * hb;
+    H[j][j] = zc(cs[j] * a.x + sr, cs[j] * a.y + si);
+    const double2 gj = g[j], ng = zmul(zconj(sn[j]), gj);
+    g[j + 1] = zc(-ng.x, -ng.y);
+    g[j] = zc(cs[j] * gj.x, cs[j] * gj.y);
+  }
+#pragma unroll
+  for (int j = kGRv - 1; j >= 0; --j) {
+    y[j] = zc(0.0, 0.0);
+    if (j >= m) continue;
+    double2 r = g[j];
+#pragma unroll
+    for (int k = j + 1; k < kGRv; ++k) {
+      const double2 p = zmul(H[j][k], y[k]);
+      if (k < m) r = zc(r.x - p.x, r.y - p.y);
+    }
+    const double2 p = H[j][j];
+    const double w = 1.0 / (p.x * p.x + p.y * p.y);
+    if (p.x != 0.0 || p.y != 0.0) y[j] = zc((r.x * p.x + r.y * p.y) * w, (r.y * p.x - r.x * p.y) * w);
+    yls[j] = zc(y[j].x * sc[j], y[j].y * sc[j]);
+  }
+}
+
+// RPT rows per work-item, W slots (the widest row of A, with its diagonal)
+template <class T, int RPT, int W>
+__global__ __launch_bounds__(kGR) void k_hz_gmres_r(CEll<T> A, GEll G, const T* __restrict__ invdeg, int B,
+                                                   const cx<T>* __restrict__ f, cx<T>* __restrict__ u, T theta, T eta,
+                                                   WK<T> WB, int K, int v) {
+  __shared__ double red[2][8 * 9];
+  __shared__ double2 H[(kGRv + 1) * kGRv];
+  __shared__ double2 yls[kGRv];
+  extern __shared__ __align__(16) unsigned char hz_dyn[];
+  const int b = blockIdx.x, n = A.n, t0 = threadIdx.x;
+  cx<T>* const lds = reinterpret_cast<cx<T>*>(hz_dyn);
+  int cur = 0, rb = 0;            // offset of the buffer that the next product gathers (0 or n); reduction buffer
+
+  unsigned ic[RPT];
+  bool ok[RPT];
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    ok[r] = t0 + r * kGR < n;
+    ic[r] = ok[r] ? t0 + r * kGR : n - 1;
+  }
+  // slot q of an ELL array: a uniform base, so that a row's loads share one offset register
+  auto slot = [&](auto* p, int q, int w) __attribute__((always_inline)) { return p + (size_t)(q < w ? q : 0) * n; };
+  int ac[RPT][W];
+  cx<T> av[RPT][W];
+#pragma unroll
+  for (int r = 0; r < RPT; ++r)
+#pragma unroll
+    for (int q = 0; q < W; ++q) {   // slots past the width repeat the first column with value 0
+      ac[r][q] = slot(A.col, q, A.w)[ic[r]];
+      av[r][q] = slot(A.val, q, A.w)[ic[r]];
+      if (q >= A.w) av[r][q] = mkc<T>(0, 0);
+    }
+  cx<T> R[RPT], D0[RPT], w[RPT], V[kGRv][RPT];
+  auto store = [&](const cx<T> (&z)[RPT]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < RPT; ++r)
+      if (ok[r]) lds[cur + ic[r]] = z[r];
+  };
+  // z = A x with x at lds + cur
+  auto amul = [&](cx<T> (&z)[RPT]) __attribute__((always_inline)) {
+    const cx<T>* x = lds + cur;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      cx<T> t[W];
+#pragma unroll
+      for (int q = 0; q < W; ++q) t[q] = x[ac[r][q]];
+      T ar = 0, ai = 0;
+#pragma unroll
+      for (int q = 0; q < W; ++q) {
+        ar += av[r][q].x * t[q].x - av[r][q].y * t[q].y;
+        ai += av[r][q].x * t[q].y + av[r][q].y * t[q].x;
+      }
+      z[r] = mkc<T>(ar, ai);
+    }
+  };
+
+  // 1. residual
+  cx<T> f0[RPT], u0[RPT];          // the rows' u stays in registers for the update
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    R[r] = u0[r] = u[(size_t)ic[r] * B + b];
+    f0[r] = f[(size_t)ic[r] * B + b];
+  }
+  store(R);
+  __syncthreads();
+  amul(w);
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) R[r] = mkc<T>(f0[r].x - w[r].x, f0[r].y - w[r].y);
+  // 2. initial guess d0 = theta Phi_B(r) (Horner over the neighbour mean; the first hop forms
+  // W_{K-1} r + W_K (M r), since the feature mixing commutes with it)
+  if (K == 0) {
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      const cx<T> t = mixw(WB.w[0], R[r]);
+      D0[r] = mkc<T>(theta * t.x, theta * t.y);
+    }
+  } else {
+    cur = n - cur;
+    store(R);
+    __syncthreads();
+    for (int k = K - 1; k >= 0; --k) {
+      const T s = k == 0 ? theta : (T)1;
+      const cx<T>* yc = lds + cur;
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        T mr = 0, mi = 0;
+        int jj[W];
+        cx<T> tv[W];
+#pragma unroll
+        for (int q = 0; q < W; ++q) jj[q] = slot(G.col, q, G.w)[ic[r]];
+#pragma unroll
+        for (int q = 0; q < W; ++q) tv[q] = yc[jj[q]];
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+          const bool on = q < G.w && jj[q] != (int)ic[r];
+          mr = on ? mr + tv[q].x : mr;
+          mi = on ? mi + tv[q].y : mi;
+        }
+        cx<T> t = mixw(WB.w[k], R[r]);
+        const T g = invdeg[ic[r]];
+        cx<T> m = mkc<T>(g * mr, g * mi);
+        if (k == K - 1) m = mixw(WB.w[K], m);
+        t.x += m.x;
+        t.y += m.y;
+        D0[r] = mkc<T>(s * t.x, s * t.y);
+      }
+      if (k > 0) {
+        cur = n - cur;
+        store(D0);
+        __syncthreads();
+      }
+    }
+  }
+  // 3. r0 = r - A d0 and beta = ||r0||
+  cur = n - cur;
+  store(D0);
+  __syncthreads();
+  amul(w);
+  double acc[9];
+  acc[0] = 0.0;
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    // rows past the end hold zeros from here on (a factor, not a branch around the products):
+    // they add nothing to a sum
+    const T one = ok[r] ? (T)1 : (T)0;
+    w[r] = V[0][r] = mkc<T>((R[r].x - w[r].x) * one, (R[r].y - w[r].y) * one);
+    acc[0] += (double)w[r].x * w[r].x + (double)w[r].y * w[r].y;
+  }
+  cur = n - cur;
+  store(w);
+  hz_group_sum<1>(acc, red[rb]);
+  rb ^= 1;
+  const double beta = sqrt(acc[0]);
+  // 4. Arnoldi with a lazily normalised basis: slot t holds Vt_t and the basis vector is
+  // v_t = sc[t] Vt_t.  A step is the product with the first pass's dot products and norm, the first
+  // update with the second pass's, and a second update only when the first cancelled more than
+  // 1 - 1/sqrt 2 of the norm (Kahan-Parlett).
+  double sc[kGRv + 1];
+#pragma unroll
+  for (int t = 0; t <= kGRv; ++t) sc[t] = 0.0;
+  int m = 0;
+  if (beta > 0.0) {
+    sc[0] = 1.0 / beta;
+    if (t0 < (kGRv + 1) * kGRv) H[t0] = zc(0.0, 0.0);
+    m = v;
+    // dots of w against the basis so far and its norm: acc[2t], acc[2t + 1], acc[2 (j + 1)]
+    auto dots = [&](auto jc) __attribute__((always_inline)) {
+      constexpr int j = decltype(jc)::value;
+#pragma unroll
+      for (int k = 0; k < 2 * (j + 1) + 1; ++k) acc[k] = 0.0;
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        acc[2 * (j + 1)] += (double)w[r].x * w[r].x + (double)w[r].y * w[r].y;
+#pragma unroll
+        for (int t = 0; t <= j; ++t) {
+          const cx<T> q = V[t][r];          // conj(q) w
+          acc[2 * t] += (double)q.x * w[r].x + (double)q.y * w[r].y;
+          acc[2 * t + 1] += (double)q.x * w[r].y - (double)q.y * w[r].x;
+        }
+      }
+    };
+    auto step = [&](auto jc) __attribute__((always_inline)) -> bool {
+      constexpr int j = decltype(jc)::value, NV = 2 * (j + 1) + 1;
+      const T s = (T)sc[j];
+      amul(w);
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        const T sr = ok[r] ? s : (T)0;
+        w[r] = mkc<T>(w[r].x * sr, w[r].y * sr);
+      }
+      dots(jc);
+      hz_group_sum<NV>(acc, red[rb]);
+      rb ^= 1;
+      cur = n - cur;
+      const double w2 = acc[NV - 1];
+      double hn2 = 0.0;
+      for (int pass = 0; pass < 2; ++pass) {
+        T cr[j + 1], ci[j + 1];
+#pragma unroll
+        for (int t = 0; t <= j; ++t) {
+          cr[t] = (T)(acc[2 * t] * sc[t] * sc[t]);
+          ci[t] = (T)(acc[2 * t + 1] * sc[t] * sc[t]);
+          if (t0 == 0) {
+            const double2 h = H[t * kGRv + j];
+            H[t * kGRv + j] = zc(h.x + acc[2 * t] * sc[t], h.y + acc[2 * t + 1] * sc[t]);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < RPT; ++r)
+#pragma unroll
+          for (int t = 0; t <= j; ++t) {
+            const cx<T> q = V[t][r];
+            w[r].x -= cr[t] * q.x - ci[t] * q.y;
+            w[r].y -= cr[t] * q.y + ci[t] * q.x;
+          }
+        if (j + 1 < v) store(w);
+        dots(jc);
+        hz_group_sum<NV>(acc, red[rb]);
+        rb ^= 1;
+        hn2 = acc[NV - 1];
+        if (!(hn2 < 0.5 * w2)) break;
+      }
+      const double hn = sqrt(hn2);
+      if (t0 == 0) H[(j + 1) * kGRv + j] = zc(hn, 0.0);
+      if (hn == 0.0) {
+        m = j + 1;
+        return false;
+      }
+      sc[j + 1] = 1.0 / hn;
+      if constexpr (j + 1 < kGRv) {
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) V[j + 1][r] = w[r];
+      }
+      return j + 1 < v;
+    };
+    using std::integral_constant;
+    if (step(integral_constant<int, 0>{}) && step(integral_constant<int, 1>{}) && step(integral_constant<int, 2>{}))
+      step(integral_constant<int, 3>{});
+    __syncthreads();
+    // with the lazy scales folded into the coefficients: v_t y_t = Vt_t (sc[t] y_t)
+    if (t0 == 0) hz_lsq_r(H, m, beta, sc, yls);
+    __syncthreads();
+  }
+  // 5. u += eta (d0 + V y)
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    double dr = D0[r].x, di = D0[r].y;
+#pragma unroll
+    for (int t = 0; t < kGRv; ++t) {
+      if (t < m) {
+        const double2 y = yls[t];
+        dr += y.x * V[t][r].x - y.y * V[t][r].y;
+        di += y.x * V[t][r].y + y.y * V[t][r].x;
+      }
+    }
+    if (ok[r]) u[(size_t)ic[r] * B + b] = mkc<T>(u0[r].x + eta * (T)dr, u0[r].y + eta * (T)di);
+  }
+}
+
 // ------------------------------------------------------------------ FP64 Krylov sweeps (outer FGMRES)
 // Rows are split into nblk chunks; 2^lb >= B lanes per row, 256 >> lb rows per pass.
 #define HZ_KR                                                          \
@@ -1071,6 +1455,16 @@ namespace {
 
 template <class T>
 struct HzEngine final : mgh_ctx {
+  using GmresFn = void (*)(CEll<T>, GEll, const T*, int, const cx<T>*, cx<T>*, T, T, WK<T>, int, int);
+  // The GMRES smoothing step with rows in registers for a level of n rows of w slots (null: the sweep
+  // form, for more than kGRv steps, wider rows, or more than three rows per work-item: with nine, or
+  // five of 1024, A's rows no longer fit the registers and reading them again in every product took
+  // FP32 65 x 65 levels from 145 to 100 us but FP64 ones from 208 to 225)
+  static GmresFn gmres_fn(int n, int w, int v) {
+    if (v > kGRv || w > kGRw || w < 1 || n > 3 * kGR) return nullptr;
+    if (n <= kGR) return w <= 7 ? &k_hz_gmres_r<T, 1, 7> : &k_hz_gmres_r<T, 1, 8>;
+    return w <= 7 ? &k_hz_gmres_r<T, 3, 7> : &k_hz_gmres_r<T, 3, 8>;
+  }
   struct Lv {
     int n = 0;
     CEll<T> A{};
@@ -1082,6 +1476,7 @@ struct HzEngine final : mgh_ctx {
     cx<T>* scr = nullptr;        // GMRES scratch (global), or null when the step runs in LDS
     size_t lds = 0;              // dynamic LDS bytes of the GMRES step
     int gmode = 0;               // placement of its vectors (k_hz_gmres MODE)
+    GmresFn gfn = nullptr;       // the form with its rows in registers, where there is one
     int kind = MGH_JACOBI, pre = 0, post = 0;
   };
   int J = 0, Bn = 0, lb = 0, KB = 0, KR = 0, KP = 0, v = 4;
@@ -1190,7 +1585,10 @@ struct HzEngine final : mgh_ctx {
       H_LAUNCH();
       return conv(l, WB[l], KB, L.D, u, (T)eta[l], true, st);
     }
-    if (L.gmode == 1)
+    if (L.gfn) {
+      hipLaunchKernelGGL(L.gfn, dim3(Bn), dim3(kGR), L.lds, st, L.A, L.G, L.invdeg, Bn, f, u, (T)theta[l], (T)eta[l],
+                         WB[l], KB, v);
+    } else if (L.gmode == 1)
       hipLaunchKernelGGL((k_hz_gmres<T, 1>), dim3(Bn), dim3(kGT), L.lds, st, L.A, L.G, L.invdeg, Bn, f, u,
                          (T)theta[l], (T)eta[l], WB[l], KB, v, L.scr);
     else if (L.gmode == 2)
@@ -1642,7 +2040,10 @@ struct HzEngine final : mgh_ctx {
         H_TRY(mem.alloc(&L.Tb, nB));
         if (L.kind == MGH_GMRES) {
           const size_t all = (size_t)hz_slots(v) * n * sizeof(cx<T>), basis = (size_t)v * n * sizeof(cx<T>);
-          if (all <= (size_t)kGmresLds) {
+          L.gfn = gmres_fn(n, w, v);
+          if (L.gfn) {
+            L.lds = 2 * (size_t)n * sizeof(cx<T>);   // at most 48 KB
+          } else if (all <= (size_t)kGmresLds) {
             L.gmode = 1;
             L.lds = all;
           } else if (v >= 3 && basis <= (size_t)kGmresLds) {
