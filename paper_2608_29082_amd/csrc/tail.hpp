@@ -308,6 +308,7 @@ __device__ __forceinline__ void tail_visit(const TailArgs<C>& T, C* sm, uint32_t
   // u = (uz ? 0 : u) + scale Phi(x) (K == 0: + a0 x), to LDS
   auto add = [&](const C* c, int K, C scale, C a0) {
     if (K == 0) {
+      tail_sync<WAVE>();             // x may come from a residual: every read of u ends before it changes
       if (act)
 #pragma unroll
         for (int r = 0; r < RPT; ++r) u[r] = tfma(a0, x[r], uz ? C(0) : u[r]);

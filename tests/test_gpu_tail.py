@@ -84,3 +84,22 @@ def test_tail_variants(prec, n, width, graph, agg):
     errs = [elem_rel(o[2], want) for o in outs]
     print(f"{prec} n={n} width={width} graph={graph} {agg}: cycle errors {errs[0]:.1e} {errs[1]:.1e}", flush=True)
     assert max(errs) <= TOL[prec]
+
+
+@pytest.mark.parametrize("prec,n", [("fp32", 60), ("fp32", 900), ("fp32", 2100), ("fp32", 4000), ("fp64", 1500)])
+def test_tail_without_convolutions(prec, n):
+    """K = 0 (the classical cycle): no convolution's barriers lie between a residual's reads of the
+    iterate and its update.  The cycle from zero against the oracle, and the same bits every time."""
+    import torch
+    from paper_2608_29082_amd import binding as Bd
+    A, P = _hierarchy(n, 6, n)
+    J, B = len(A), 3
+    flat = C.identity_params(J, 0, 0, 0)
+    f = C.rng(11, 3, n).standard_normal((n, B))
+    ctx = Bd.Context(A, P, flat, 0, 0, 0, precision=prec, nrhs=B)
+    fd = to_dev(f, torch.float64)
+    outs = [to_np(ctx.refine_step(fd, torch.zeros_like(fd))) for _ in range(20)]
+    want = O.lmg(O.make_levels(A, P), O.unpack(flat, J, 0, 0, 0), 0, f, np.zeros_like(f))
+    assert elem_rel(outs[0], want) <= TOL[prec]
+    assert all(np.array_equal(o, outs[0]) for o in outs)
+    ctx.close()
