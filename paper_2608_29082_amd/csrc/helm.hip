@@ -24,6 +24,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "lanes.hpp"
 #include "mgh.h"
 
 namespace {
@@ -632,36 +633,6 @@ constexpr int kGR = 512;
 constexpr int kGRv = 4;          // GMRES steps of this form (at most)
 constexpr int kGRw = 8;          // slots per row (at most)
 
-template <int CTRL>
-__device__ __forceinline__ double hz_dpp(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-__device__ __forceinline__ double hz_pair(unsigned lo, unsigned hi) {
-  return __longlong_as_double(((long long)hi << 32) | lo);
-}
-// v + the value of the lane 16 (32) away, in both
-__device__ __forceinline__ double hz_add16(double v) {
-  const long long b = __double_as_longlong(v);
-  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
-  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-  return hz_pair(l[0], h[0]) + hz_pair(l[1], h[1]);
-}
-__device__ __forceinline__ double hz_add32(double v) {
-  const long long b = __double_as_longlong(v);
-  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
-  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-  return hz_pair(l[0], h[0]) + hz_pair(l[1], h[1]);
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppRor4 = 0x124, kDppRor8 = 0x128, kDppHalfMirror = 0x141;
-__device__ __forceinline__ double hz_lane(double v, int lane) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 // Sums over the workgroup (8 wavefronts) of NV values per work-item (NV = 1, 3,
 // 5, 7 or 9: dot products and, last, a norm), in a fixed order, the totals
 // uniform in every work-item.  red: 8 x 9 doubles, another buffer for every
@@ -669,6 +640,7 @@ __device__ __forceinline__ double hz_lane(double v, int lane) {
 // one's reads).
 template <int NV>
 __device__ __forceinline__ void hz_group_sum(double (&a)[9], double* red) {
+  using namespace mgl;
   const int ln = threadIdx.x & 63, wv = threadIdx.x >> 6;
   double x;                       // lane l: the wavefront's sum of value l & 7 (of the first NV - 1)
   const bool b0 = ln & 1, b1 = ln & 2, b2 = ln & 4;
@@ -677,35 +649,30 @@ __device__ __forceinline__ void hz_group_sum(double (&a)[9], double* red) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const double lo = 2 * k < NV - 1 ? a[2 * k] : 0.0, hi = 2 * k + 1 < NV - 1 ? a[2 * k + 1] : 0.0;
-      p[k] = (b0 ? hi : lo) + hz_dpp<kDppXor1>(b0 ? lo : hi);
+      p[k] = (b0 ? hi : lo) + lane_dpp<kDppXor1>(b0 ? lo : hi);
     }
-    const double q0 = (b1 ? p[1] : p[0]) + hz_dpp<kDppXor2>(b1 ? p[0] : p[1]);
-    const double q1 = (b1 ? p[3] : p[2]) + hz_dpp<kDppXor2>(b1 ? p[2] : p[3]);
-    x = (b2 ? q1 : q0) + hz_dpp<kDppRor4>(b2 ? q0 : q1);
-    x += hz_dpp<kDppRor8>(x);
-    x = hz_add32(hz_add16(x));
+    const double q0 = (b1 ? p[1] : p[0]) + lane_dpp<kDppXor2>(b1 ? p[0] : p[1]);
+    const double q1 = (b1 ? p[3] : p[2]) + lane_dpp<kDppXor2>(b1 ? p[2] : p[3]);
+    x = (b2 ? q1 : q0) + lane_dpp<kDppRor4>(b2 ? q0 : q1);
+    x += lane_dpp<kDppRor8>(x);
+    x = lane_add32(lane_add16(x));
   }
-  double y = a[NV - 1];
-  y += hz_dpp<kDppXor1>(y);
-  y += hz_dpp<kDppXor2>(y);
-  y += hz_dpp<kDppHalfMirror>(y);
-  y += hz_dpp<kDppRor8>(y);
-  y = hz_add32(hz_add16(y));
+  double y = wave_sum(a[NV - 1]);
   if (NV > 1 && ln < 8) red[wv * 9 + ln] = x;
   if (ln == 8) red[wv * 9 + 8] = y;
   __syncthreads();
   if constexpr (NV > 1) {
     x = red[(ln >> 3) * 9 + (ln & 7)];
-    x += hz_dpp<kDppRor8>(x);
-    x = hz_add32(hz_add16(x));
+    x += lane_dpp<kDppRor8>(x);
+    x = lane_add32(lane_add16(x));
 #pragma unroll
-    for (int k = 0; k < NV - 1; ++k) a[k] = hz_lane(x, k);
+    for (int k = 0; k < NV - 1; ++k) a[k] = lane_get(x, k);
   }
   y = red[(ln & 7) * 9 + 8];
-  y += hz_dpp<kDppXor1>(y);
-  y += hz_dpp<kDppXor2>(y);
-  y += hz_dpp<kDppHalfMirror>(y);
-  a[NV - 1] = hz_lane(y, 0);
+  y += lane_dpp<kDppXor1>(y);
+  y += lane_dpp<kDppXor2>(y);
+  y += lane_dpp<kDppHalfMirror>(y);
+  a[NV - 1] = lane_get(y, 0);
 }
 
 // Least squares min || beta e_1 - H y || of an (m + 1) x m Hessenberg matrix with

@@ -244,6 +244,9 @@ struct Engine final : EngineBase {
   // coarse tail (levels tail_lt .. J-1 in LDS, one workgroup per column)
   int tail_lt = -1;                 // shallowest level whose tail fits in LDS
   int tail_own = -1;                // first of its levels that have no fused-convolution tiles
+  int btail_lt = -1;                // first level of the reverse sweep's tail
+  TailBwdArgs<C> btail{};
+  size_t btail_bytes = 0;
   std::vector<TailArgs<C>> tails;   // launch arguments for start levels tail_lt .. J-2
   std::vector<size_t> tail_bytes;
   char* wsbase = nullptr;
@@ -283,23 +286,27 @@ struct Engine final : EngineBase {
   const double* cR(int l) const { return cB(l) + pl.KB + 1; }
   const double* cP(int l) const { return cR(l) + pl.KR + 1; }
 
-  // slots of the reverse sweep, in launch order (kind, level, k)
-  void enum_slots(int l) {
+  // slots of the reverse sweep, in launch order (kind, level, k): a slot's partial sums are one per
+  // block of the level's sweeps, or one per column in the tail (most: the larger of both, for sizes)
+  void enum_slots(int l, bool most) {
     const int J = pl.J;
     if (l == J - 1) return;
+    const int rb = (int)d[l].rblocks, cnt = most ? std::max(rb, pl.B) : (btail_lt >= 0 && l >= btail_lt ? pl.B : rb);
     auto add = [&](int kind, int K) {
       for (int k = 0; k <= K; ++k) {
         h_desc.push_back(kind); h_desc.push_back(l); h_desc.push_back(k);
-        h_cnt.push_back((int)d[l].rblocks);
+        h_cnt.push_back(cnt);
         h_off.push_back(h_off.empty() ? 0 : h_off.back() + h_cnt[h_cnt.size() - 2]);
       }
     };
     for (int j = 0; j < pl.nu_post; ++j) add(0, pl.KB);
     add(2, pl.KP);
-    enum_slots(l + 1);
+    enum_slots(l + 1, most);
     add(1, pl.KR);
     for (int j = 0; j < pl.nu_pre; ++j) add(0, pl.KB);
   }
+  int slots_down() const { return pl.nu_post * (pl.KB + 1) + pl.KP + 1; }   // of one level, before the coarser ones
+  int slots_up() const { return pl.KR + 1 + pl.nu_pre * (pl.KB + 1); }      // and after them
 
   // launch shapes of level l's row sweeps at the current cycle width
   void level_launch(int l) {
@@ -432,7 +439,7 @@ struct Engine final : EngineBase {
     dprm = bp.take<double>(pl.params.size());
     if (bwd()) {
       h_off.clear(); h_cnt.clear(); h_desc.clear();
-      enum_slots(0);
+      enum_slots(0, true);
       nslots = (int)h_cnt.size();
       const long tot = nslots ? h_off.back() + h_cnt.back() : 0;
       dpart = bp.take<double>(tot);
@@ -580,11 +587,6 @@ struct Engine final : EngineBase {
       }
     }
     MG_TRY(up(dprm, pl.params, st));
-    if (bwd()) {
-      HIP_TRY(hipMemcpyAsync(doff, h_off.data(), h_off.size() * sizeof(long), hipMemcpyHostToDevice, st));
-      MG_TRY(upi(dcnt, h_cnt, st));
-      MG_TRY(upi(ddesc, h_desc, st));
-    }
     int info = 0;
     HIP_TRY(hipMemcpyAsync(hcount, dinfo, sizeof(int), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
@@ -594,6 +596,15 @@ struct Engine final : EngineBase {
     if (info != 0) return fail(MG_ERR_SHAPE, "coarsest matrix is singular (zero pivot in column " + std::to_string(info - 1) + ")");
     MG_TRY(setup_tiles(st));
     MG_TRY(setup_tail());
+    if (bwd()) {
+      MG_TRY(setup_bwd_tail());
+      h_off.clear(); h_cnt.clear(); h_desc.clear();
+      enum_slots(0, false);
+      HIP_TRY(hipMemcpyAsync(doff, h_off.data(), h_off.size() * sizeof(long), hipMemcpyHostToDevice, st));
+      MG_TRY(upi(dcnt, h_cnt, st));
+      MG_TRY(upi(ddesc, h_desc, st));
+      HIP_TRY(hipStreamSynchronize(st));
+    }
     sizes.resize(J);
     widths.resize(J);
     for (int l = 0; l < J; ++l) { sizes[l] = pl.lv[l].n; widths[l] = pl.lv[l].off.w; }
@@ -612,6 +623,13 @@ struct Engine final : EngineBase {
         if (any) w = std::max(w, k + 1);
       }
     return w;
+  }
+  // rows per work-item (0: generic sweeps) and slots of level l in the tail
+  void tail_variant(int l, int& rpt, int& w) const {
+    w = used_slots(l);
+    rpt = (pl.lv[l].n + kTailThreads - 1) / kTailThreads;
+    if (rpt > tail_max_rpt<C>() || w > kTailW || d[l].L.w < 1 || d[l].L.wg < 1) rpt = 0;
+    if (d[l].L.gcol != d[l].L.col) w = kTailW + 1;
   }
   // LDS layout of the tail from level lt; returns its size in bytes
   size_t tail_layout(int lt, TailArgs<C>& t) const {
@@ -656,13 +674,7 @@ struct Engine final : EngineBase {
     auto r4 = [](long x) { return (x + 3) / 4 * 4; };
     TailArgs<C> proto{};
     std::vector<int> rpt(J, 0), wu(J, 0);
-    auto variant = [&](int l) {
-      const int n = pl.lv[l].n;
-      wu[l] = used_slots(l);
-      rpt[l] = (n + kTailThreads - 1) / kTailThreads;
-      if (rpt[l] > tail_max_rpt<C>() || wu[l] > kTailW || d[l].L.w < 1 || d[l].L.wg < 1) rpt[l] = 0;
-      if (d[l].L.gcol != d[l].L.col) wu[l] = kTailW + 1;
-    };
+    auto variant = [&](int l) { tail_variant(l, rpt[l], wu[l]); };
     auto fits = [&](int lt) {
       if (lt < 0 || J - lt > kTailMaxLevels) return false;
       long old = 4 * r4(pl.lv[lt].n);
@@ -714,6 +726,73 @@ struct Engine final : EngineBase {
       tails.push_back(t);
       tail_bytes.push_back(bytes);
     }
+    return MG_OK;
+  }
+
+  // The levels whose reverse sweep runs as one launch (k_tail_bwd): from the coarsest up while their
+  // rows fit the register variants and the LDS.  Not with BF16 intermediates, which the per-level
+  // sweeps round, nor where the reverse sweep is refused (bwd_ok).
+  mg_status setup_bwd_tail() {
+    btail_lt = -1;
+    const int J = pl.J;
+    if (!std::is_same<TH, TU>::value || (pl.flags & MG_FLAG_NO_TAIL) || !pl.sym_all || pl.nv) return MG_OK;
+    int dev = 0, maxlds = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    HIP_TRY(hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    const size_t dots = (size_t)std::max(slots_down(), slots_up()) * 16 * sizeof(double);
+    TailBwdArgs<C> a{};
+    size_t bytes = 0;
+    int lt = J - 1;
+    std::vector<int> rpt(J, 0), wu(J, 0);
+    auto layout = [&](int l0, TailBwdArgs<C>& t) {
+      for (int l = l0; l < J - 1; ++l) t.T.lv[l - l0].rpt = rpt[l];
+      return (tail_layout(l0, t.T) + 15) / 16 * 16;
+    };
+    while (lt > 0 && J - (lt - 1) <= kTailMaxLevels) {
+      const int l = lt - 1;
+      tail_variant(l, rpt[l], wu[l]);
+      rpt[l] = tail_bwd_rpt<C>(rpt[l]);
+      TailBwdArgs<C> t{};
+      const size_t b = rpt[l] ? layout(l, t) : 0;
+      if (!b || b + dots > (size_t)maxlds) break;
+      bytes = b;
+      lt = l;
+    }
+    if (lt > J - 2) return MG_OK;
+    layout(lt, a);
+    const void* fn = wgt() ? reinterpret_cast<const void*>(&k_tail_bwd<true, C>)
+                           : reinterpret_cast<const void*>(&k_tail_bwd<false, C>);
+    btail_bytes = bytes + dots;
+    if (btail_bytes > 65536 &&
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)btail_bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return MG_OK;   // large dynamic LDS unavailable: keep the per-level sweeps
+    }
+    btail_lt = lt;
+    a.off_dot = (int)bytes;
+    a.T.KB = pl.KB; a.T.KR = pl.KR; a.T.KP = pl.KP;
+    a.T.nu_pre = pl.nu_pre; a.T.nu_post = pl.nu_post; a.T.per = per();
+    a.T.prm = dprm + (size_t)lt * per();
+    a.T.Ainv = Ainv;
+    a.T.lt = lt;
+    const int nl = J - lt;
+    for (int q = 0; q < nl; ++q) {
+      const DL& x = d[lt + q];
+      a.T.lv[q].L = x.L;
+      if (q + 1 == nl) break;
+      a.T.lv[q].P = x.P;
+      a.T.lv[q].R = x.R;
+      a.T.lv[q].w = wu[lt + q];
+      a.b[q].PT = x.PT;
+      a.b[q].RT = x.RT;
+      // S_0 .. S_{nu-1}, Rv, X, ut and g follow each other at one distance (carve)
+      const size_t nv = (size_t)pl.lv[lt + q].n * pl.B * sizeof(TU);
+      a.b[q].stride = (long)(((nv + 255) & ~size_t(255)) / sizeof(TU));
+      a.b[q].keep = reinterpret_cast<C*>(pl.nu_pre + pl.nu_post ? (void*)x.S[0] : (void*)x.Rv);
+      a.b[q].slot0 = q * slots_down();
+      a.b[q].slot1 = a.b[q].slot0 + slots_down() + (nl - 2 - q) * (slots_down() + slots_up());
+    }
+    btail = a;
     return MG_OK;
   }
 
@@ -1711,6 +1790,22 @@ struct Engine final : EngineBase {
         hipLaunchKernelGGL((k_fill0<TU>), dim3(nblocks(nB)), dim3(256), 0, st, nB, gul);
         LAUNCH_OK();
       }
+      return MG_OK;
+    }
+    if (btail_lt >= 0 && l >= btail_lt) {
+      // levels l .. J-1 in one launch (l is the first of them: the levels above call it)
+      if (l != btail_lt) return fail(MG_ERR_STATE, "reverse sweep entered its tail below the first level");
+      TailBwdArgs<C> a = btail;
+      for (int q = 0; q + 1 < a.T.nl; ++q) {
+        a.b[q].f = ck.f[l + q];
+        a.b[q].ec = ck.u[l + q + 1];
+      }
+      if (slot + a.T.nl - 1 > nslots) return fail(MG_ERR_STATE, "reverse sweep slot overflow");
+      a.part = dpart + h_off[slot];
+      WG_SPLIT(hipLaunchKernelGGL((k_tail_bwd<WGv, C>), dim3(B()), dim3(kTailThreads), btail_bytes, st, a, B(), uin,
+                                  gout, gfl, gul));
+      LAUNCH_OK();
+      slot += (a.T.nl - 1) * (slots_down() + slots_up());
       return MG_OK;
     }
     DL& D = d[l];

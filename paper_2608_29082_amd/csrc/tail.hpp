@@ -23,6 +23,7 @@
 // read the operator from global memory in every sweep.
 #pragma once
 #include "kernels.hpp"
+#include "lanes.hpp"
 
 namespace mgl {
 
@@ -106,56 +107,41 @@ __host__ __device__ constexpr int tail_stride(int rpt, int n, int size) {
   return (n <= 64 ? 64 : rpt * kTailThreads) * size + 64;
 }
 
-// RPT rows per work-item, W slots; WAVE: n <= 64, one wavefront; SAME: the
-// graph's neighbours are A's; VC / GC: the operator's values / the edge weights
-// are held in registers (else they are read again in every sweep, from the L2)
+// The rows of one work-item in a level visit.  RPT rows per work-item, W slots;
+// WAVE: n <= 64, one wavefront; SAME: the graph's neighbours are A's; VC / GC: the
+// operator's values / the edge weights are held in registers (else they are
+// read again in every sweep, from the L2).
 template <int RPT, int W, bool WAVE, bool SAME, bool VC, bool GC, bool WG, class C>
-__device__ __forceinline__ void tail_visit(const TailArgs<C>& T, C* sm, uint32_t wk, const C* prm, int q, int what,
-                                           int nsm, int uz) {
-  const TailLevel<C>& tl = T.lv[q];
-  const Lvl<C>& L = tl.L;
-  const int n = L.n, tid = threadIdx.x;
-  constexpr int nt = WAVE ? 64 : kTailThreads;
-  constexpr uint32_t ST = tail_stride(RPT, WAVE ? 64 : RPT * kTailThreads, sizeof(C));
-  constexpr uint32_t S = 0, Y = ST, V = 2 * ST;   // work buffers: two for the hops, the iterate
-  if (WAVE && tid >= 64) return;
-  const bool act = (tid & ~63) < n;      // wave-uniform: this wavefront has rows
-  const int ord = q < T.nord;
-  C *U = sm + tl.off_u, *F = sm + tl.off_f;
-  const C* p = prm + q * T.per;
-  const C *cB = p + 2, *cR = cB + T.KB + 1, *cP = cR + T.KR + 1;
-  // per-column operators: value (k, i) of this workgroup's column at (k ld + i) vm + vb
-  const int vm = L.vs ? L.vs : 1, vb = L.vs ? vcol(L, (int)blockIdx.x) : 0;
-  auto slotv = [&](int k, int i) { return L.val[(k < L.w ? k : 0) * L.ld * vm + (i * vm + vb)]; };
-  auto slotw = [&](int k, int i) { return L.gval[(k < L.wg ? k : 0) * L.ld + i]; };
-  const bool pro = (what & (TV_PRO | TV_PRO_SET)) != 0;
+struct TailRows {
+  static constexpr int nt = WAVE ? 64 : kTailThreads;
+  static constexpr uint32_t ST = tail_stride(RPT, WAVE ? 64 : RPT * kTailThreads, sizeof(C));
+  static constexpr uint32_t S = 0, Y = ST, V = 2 * ST;   // work buffers: two for the hops, the iterate
+  static constexpr uint32_t RS = nt * sizeof(C);
 
-  const uint32_t own = wk + tid * (uint32_t)sizeof(C);     // row r at own + r * RS
-  constexpr uint32_t RS = nt * sizeof(C);
+  const Lvl<C>& L;
+  const int n, tid, ord;
+  const uint32_t wk, own;         // first work buffer; this work-item's first row in it (row r at own + r RS)
+  const bool act;                 // wave-uniform: this wavefront has rows
+  const int vm, vb;               // per-column operators: value (k, i) at (k ld + i) vm + vb
   int ic[RPT];
   bool ok[RPT];
   uint32_t aa[RPT][W], ga[SAME ? 1 : RPT][SAME ? 1 : W];
   C av[VC ? RPT : 1][VC ? W : 1], gw[WG && GC ? RPT : 1][WG && GC ? W : 1];
-  C dg[RPT], ida[RPT], idg[RPT], f[RPT], u[RPT], x[RPT], v[RPT];
-  // a prolongation of two slots per row (linear interpolation on nested meshes), loaded first
-  const Xfer<C>& P = tl.P;
-  int pj[RPT][2];
-  C pw[RPT][2];
-  if (act) {
+  C dg[RPT], ida[RPT], idg[RPT];
+
+  __device__ __forceinline__ TailRows(const Lvl<C>& L_, uint32_t wk_, int ord_)
+      : L(L_), n(L_.n), tid(threadIdx.x), ord(ord_), wk(wk_), own(wk_ + threadIdx.x * (uint32_t)sizeof(C)),
+        act((int)(threadIdx.x & ~63u) < L_.n), vm(L_.vs ? L_.vs : 1), vb(L_.vs ? vcol(L_, (int)blockIdx.x) : 0) {
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
       ok[r] = tid + r * nt < n;
       ic[r] = ok[r] ? tid + r * nt : n - 1;
     }
-    if (pro && P.w == 2) {
-#pragma unroll
-      for (int r = 0; r < RPT; ++r)
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          pj[r][k] = P.col[k * P.n + ic[r]];
-          pw[r][k] = P.val[k * P.n + ic[r]];
-        }
-    }
+  }
+  __device__ __forceinline__ C slotv(int k, int i) const { return L.val[(k < L.w ? k : 0) * L.ld * vm + (i * vm + vb)]; }
+  __device__ __forceinline__ C slotw(int k, int i) const { return L.gval[(k < L.wg ? k : 0) * L.ld + i]; }
+  __device__ __forceinline__ void load() {
+    if (!act) return;
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
       const int i = ic[r];
@@ -179,71 +165,47 @@ __device__ __forceinline__ void tail_visit(const TailArgs<C>& T, C* sm, uint32_t
         if constexpr (VC) av[r][k] = k < L.w ? av[r][k] : C(0);
         if constexpr (WG && GC) gw[r][k] = k < L.wg ? gw[r][k] : C(0);
       }
-      f[r] = F[i];
-      u[r] = uz ? C(0) : U[i];
-      if (!uz && ok[r]) lds_put<C>(own + r * RS + V, u[r]);
     }
   }
-  // the restriction's row of this work-item, loaded with the level's rows where registers allow
-  constexpr bool PF = RPT == 1 || (sizeof(C) == 4 && RPT * W <= 24);
-  const Xfer<C>& R = tl.R;
-  const bool pre = PF && (what & (TV_RES | TV_RES_F)) && R.n <= nt && R.w >= 1 && R.w <= kTailW;
-  int rj[PF ? kTailW : 1];
-  C rw[PF ? kTailW : 1];
-  if constexpr (PF) {
-    if (pre && (tid & ~63) < R.n) {
-      const int e = tid < R.n ? tid : R.n - 1;
-#pragma unroll
-      for (int k = 0; k < kTailW; ++k) {
-        const int o = (k < R.w ? k : 0) * R.n;
-        rj[k] = R.col[o + e];
-        rw[k] = R.val[o + e];
-      }
+  __device__ __forceinline__ void zeros() const {
+    if (tid == 0) {
+      lds_put<C>(wk + S + n * (uint32_t)sizeof(C), C(0));
+      lds_put<C>(wk + Y + n * (uint32_t)sizeof(C), C(0));
+      lds_put<C>(wk + V + n * (uint32_t)sizeof(C), C(0));
     }
   }
-  if (tid == 0) {
-    lds_put<C>(wk + S + n * (uint32_t)sizeof(C), C(0));
-    lds_put<C>(wk + Y + n * (uint32_t)sizeof(C), C(0));
-    lds_put<C>(wk + V + n * (uint32_t)sizeof(C), C(0));
+  __device__ __forceinline__ uint32_t nb(int r, int k) const {
+    if constexpr (SAME) return aa[r][k];
+    else return ga[r][k];
   }
-  if (!uz) tail_sync<WAVE>();            // the first residual gathers u
-
-  auto nb = [&](int r, int k) { return SAME ? aa[r][k] : ga[SAME ? 0 : r][SAME ? 0 : k]; };
-  auto store = [&](uint32_t buf, const C (&z)[RPT]) {
+  __device__ __forceinline__ void store(uint32_t buf, const C (&z)[RPT]) const {
     if (act)
 #pragma unroll
       for (int r = 0; r < RPT; ++r)
         if (ok[r]) lds_put<C>(own + r * RS + buf, z[r]);
-  };
-  // x = [invdiag] (f - A u); no branch between the rows, so that all their reads are in flight together
-  auto resid = [&](int jac) {
-    if (uz) {
+  }
+  // x = f - A u with u in work buffer V; no branch between the rows, so that all their reads are in
+  // flight together
+  __device__ __forceinline__ void resid(const C (&f)[RPT], const C (&u)[RPT], C (&x)[RPT]) const {
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) x[r] = f[r];
-    } else {
+    for (int r = 0; r < RPT; ++r) {
+      C t[W], a[W];
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) {
-        C t[W], a[W];
-#pragma unroll
-        for (int k = 0; k < W; ++k) {
-          if constexpr (VC) {
-            a[k] = av[r][k];
-          } else {
-            const C w = slotv(k, ic[r]);
-            a[k] = k < L.w ? w : C(0);
-          }
+      for (int k = 0; k < W; ++k) {
+        if constexpr (VC) {
+          a[k] = av[r][k];
+        } else {
+          const C w = slotv(k, ic[r]);
+          a[k] = k < L.w ? w : C(0);
         }
-#pragma unroll
-        for (int k = 0; k < W; ++k) t[k] = lds_get<C>(aa[r][k] + V);
-        x[r] = tail_resid<W>(a, t, dg[r], u[r], f[r], ord);
       }
-    }
-    if (jac)
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) x[r] *= ida[r];
-  };
-  // v = a G y + c x with y in work buffer `buf`
-  auto hop = [&](uint32_t buf, C a, C c) {
+      for (int k = 0; k < W; ++k) t[k] = lds_get<C>(aa[r][k] + V);
+      x[r] = tail_resid<W>(a, t, dg[r], u[r], f[r], ord);
+    }
+  }
+  // neighbour sums s of the vector in work buffer `buf`
+  __device__ __forceinline__ void gsum(uint32_t buf, C (&sum)[RPT]) const {
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
       C t[W], e[WG ? W : 1], s = C(0);
@@ -276,138 +238,232 @@ __device__ __forceinline__ void tail_visit(const TailArgs<C>& T, C* sm, uint32_t
 #pragma unroll
         for (int k = 0; k < W; ++k) s += t[k];
       }
-      v[r] = hop_value(a, idg[r], s, c, x[r]);
+      sum[r] = s;
     }
-  };
+  }
+  // v = a G y + c x with y in work buffer `buf`
+  __device__ __forceinline__ void hop(uint32_t buf, C a, C c, const C (&x)[RPT], C (&v)[RPT]) const {
+    if (!act) return;
+    gsum(buf, v);
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) v[r] = hop_value(a, idg[r], v[r], c, x[r]);
+  }
   // v = sum_k c_k G^k x (Horner; K >= 1); returns the hop buffer that the last hop does not read
-  auto conv = [&](const C* c, int K) -> uint32_t {
+  __device__ __forceinline__ uint32_t conv(const C* c, int K, const C (&x)[RPT], C (&v)[RPT]) const {
     store(S, x);
     tail_sync<WAVE>();
     C a = c[K];
     int k = K - 1;
 #pragma nounroll
     for (; k >= 2; k -= 2) {
-      if (act) hop(S, a, c[k]);
+      hop(S, a, c[k], x, v);
       store(Y, v);
       tail_sync<WAVE>();
-      if (act) hop(Y, C(1), c[k - 1]);
+      hop(Y, C(1), c[k - 1], x, v);
       store(S, v);
       tail_sync<WAVE>();
       a = C(1);
     }
     if (k == 1) {
-      if (act) hop(S, a, c[1]);
+      hop(S, a, c[1], x, v);
       store(Y, v);
       tail_sync<WAVE>();
-      if (act) hop(Y, C(1), c[0]);
+      hop(Y, C(1), c[0], x, v);
       return S;
     }
-    if (act) hop(S, a, c[0]);
+    hop(S, a, c[0], x, v);
     return Y;
-  };
-  // u = (uz ? 0 : u) + scale Phi(x) (K == 0: + a0 x), to LDS
-  auto add = [&](const C* c, int K, C scale, C a0) {
+  }
+  // u = (uz ? 0 : u) + scale Phi(x) (K == 0: + a0 x), to work buffer V
+  __device__ __forceinline__ void add(const C* c, int K, C scale, C a0, int uz, const C (&x)[RPT], C (&u)[RPT]) const {
+    C v[RPT];
     if (K == 0) {
       tail_sync<WAVE>();             // x may come from a residual: every read of u ends before it changes
       if (act)
 #pragma unroll
         for (int r = 0; r < RPT; ++r) u[r] = tfma(a0, x[r], uz ? C(0) : u[r]);
     } else {
-      conv(c, K);
+      conv(c, K, x, v);
       if (act)
 #pragma unroll
         for (int r = 0; r < RPT; ++r) u[r] = hop_update(uz ? C(0) : u[r], scale, v[r]);
     }
-    uz = 0;
     store(V, u);
     tail_sync<WAVE>();
-  };
+  }
+};
 
-  if (pro) {
-    const C* E = sm + T.lv[q + 1].off_u;
-    if (act) {
-      if (P.w == 2) {
-#pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-          const C t0 = E[pj[r][0]], t1 = E[pj[r][1]];
-          C g = pw[r][0] != C(0) ? tfma(pw[r][0], t0, C(0)) : C(0);
-          x[r] = pw[r][1] != C(0) ? tfma(pw[r][1], t1, g) : g;
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-          C g = C(0);
-          for (int k = 0; k < P.w; ++k) {
-            const C w = P.val[(size_t)k * P.n + ic[r]], t = E[P.col[(size_t)k * P.n + ic[r]]];
-            g = w != C(0) ? tfma(w, t, g) : g;
-          }
-          x[r] = g;
-        }
-      }
-    }
-    if (what & TV_PRO_SET) uz = 1;
-    add(cP, T.KP, C(1), cP[0]);
-  }
-#pragma nounroll
-  for (int j = 0; j < nsm; ++j) {
-    if (act) resid(1);
-    add(cB, T.KB, p[0], p[1]);
-  }
-  if (act)   // u stays with the level (zero where nothing has been added to it yet)
+// x = (X v)_i of the rows' transfer X of two slots per row (linear interpolation on nested meshes),
+// its slots loaded ahead; other widths are read in place.  v: LDS, n_c values
+template <int RPT, class C>
+struct TailXfer2 {
+  int j[RPT][2];
+  C w[RPT][2];
+  __device__ __forceinline__ void load(const Xfer<C>& X, const int (&ic)[RPT]) {
+    if (X.w != 2) return;
 #pragma unroll
     for (int r = 0; r < RPT; ++r)
-      if (ok[r]) U[ic[r]] = u[r];
-  if (what & (TV_RES | TV_RES_F)) {
-    if (act) {
-      if (what & TV_RES) resid(0);
-      else
 #pragma unroll
-        for (int r = 0; r < RPT; ++r) x[r] = f[r];
-    }
-    uint32_t out = S;
-    if (T.KR == 0) {
-      const C a0 = cR[0];
-      if (act)
+      for (int k = 0; k < 2; ++k) {
+        j[r][k] = X.col[k * X.n + ic[r]];
+        w[r][k] = X.val[k * X.n + ic[r]];
+      }
+  }
+  __device__ __forceinline__ void apply(const Xfer<C>& X, const int (&ic)[RPT], const C* v, C (&x)[RPT]) const {
+    if (X.w == 2) {
 #pragma unroll
-        for (int r = 0; r < RPT; ++r) v[r] = tfma(a0, x[r], C(0));
-    } else {
-      out = conv(cR, T.KR);
-    }
-    store(out, v);
-    tail_sync<WAVE>();
-    const uint32_t src = wk + out;
-    C* G = sm + T.lv[q + 1].off_f;
-    if (pre) {
-      if constexpr (PF) {
-        if ((tid & ~63) < R.n) {
-          C t[kTailW], g = C(0);
-#pragma unroll
-          for (int k = 0; k < kTailW; ++k) t[k] = lds_get<C>(src + rj[k] * (uint32_t)sizeof(C));
-#pragma unroll
-          for (int k = 0; k < kTailW; ++k) g = k < R.w && rw[k] != C(0) ? tfma(rw[k], t[k], g) : g;
-          if (tid < R.n) G[tid] = g;
-        }
+      for (int r = 0; r < RPT; ++r) {
+        const C t0 = v[j[r][0]], t1 = v[j[r][1]];
+        const C g = w[r][0] != C(0) ? tfma(w[r][0], t0, C(0)) : C(0);
+        x[r] = w[r][1] != C(0) ? tfma(w[r][1], t1, g) : g;
       }
     } else {
-      for (int e = tid; e < R.n; e += nt) {
-        C g = C(0);
-        for (int k0 = 0; k0 < R.w; k0 += kTailW) {
-          int j[kTailW];
-          C w[kTailW], t[kTailW];
 #pragma unroll
-          for (int k = 0; k < kTailW; ++k) {
-            const size_t o = (size_t)(k0 + k < R.w ? k0 + k : k0) * R.n + e;
-            j[k] = R.col[o];
-            w[k] = R.val[o];
-          }
+      for (int r = 0; r < RPT; ++r) {
+        C g = C(0);
+        for (int k = 0; k < X.w; ++k) {
+          const C a = X.val[(size_t)k * X.n + ic[r]], t = v[X.col[(size_t)k * X.n + ic[r]]];
+          g = a != C(0) ? tfma(a, t, g) : g;
+        }
+        x[r] = g;
+      }
+    }
+  }
+};
+// out[i] = (X v)_i for a transfer X to at most n_c rows; v at LDS address src.  The row's slots can be
+// loaded ahead (pre)
+template <bool PF, class C>
+struct TailXfer8 {
+  int j[PF ? kTailW : 1];
+  C w[PF ? kTailW : 1];
+  bool pre;
+  __device__ __forceinline__ void load(const Xfer<C>& X, int nt, bool want) {
+    pre = PF && want && X.n <= nt && X.w >= 1 && X.w <= kTailW;
+    if constexpr (PF) {
+      const int tid = threadIdx.x;
+      if (pre && (tid & ~63) < X.n) {
+        const int e = tid < X.n ? tid : X.n - 1;
+#pragma unroll
+        for (int k = 0; k < kTailW; ++k) {
+          const int o = (k < X.w ? k : 0) * X.n;
+          j[k] = X.col[o + e];
+          w[k] = X.val[o + e];
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void apply(const Xfer<C>& X, int nt, uint32_t src, C* out) const {
+    const int tid = threadIdx.x;
+    if (pre) {
+      if constexpr (PF) {
+        if ((tid & ~63) < X.n) {
+          C t[kTailW], g = C(0);
 #pragma unroll
           for (int k = 0; k < kTailW; ++k) t[k] = lds_get<C>(src + j[k] * (uint32_t)sizeof(C));
 #pragma unroll
-          for (int k = 0; k < kTailW; ++k) g = k0 + k < R.w && w[k] != C(0) ? tfma(w[k], t[k], g) : g;
+          for (int k = 0; k < kTailW; ++k) g = k < X.w && w[k] != C(0) ? tfma(w[k], t[k], g) : g;
+          if (tid < X.n) out[tid] = g;
         }
-        G[e] = g;
+      }
+    } else {
+      for (int e = tid; e < X.n; e += nt) {
+        C g = C(0);
+        for (int k0 = 0; k0 < X.w; k0 += kTailW) {
+          int jj[kTailW];
+          C ww[kTailW], t[kTailW];
+#pragma unroll
+          for (int k = 0; k < kTailW; ++k) {
+            const size_t o = (size_t)(k0 + k < X.w ? k0 + k : k0) * X.n + e;
+            jj[k] = X.col[o];
+            ww[k] = X.val[o];
+          }
+#pragma unroll
+          for (int k = 0; k < kTailW; ++k) t[k] = lds_get<C>(src + jj[k] * (uint32_t)sizeof(C));
+#pragma unroll
+          for (int k = 0; k < kTailW; ++k) g = k0 + k < X.w && ww[k] != C(0) ? tfma(ww[k], t[k], g) : g;
+        }
+        out[e] = g;
       }
     }
+  }
+};
+
+template <int RPT, int W, bool WAVE, bool SAME, bool VC, bool GC, bool WG, class C>
+__device__ __forceinline__ void tail_visit(const TailArgs<C>& T, C* sm, uint32_t wk, const C* prm, int q, int what,
+                                           int nsm, int uz) {
+  using Rows = TailRows<RPT, W, WAVE, SAME, VC, GC, WG, C>;
+  const TailLevel<C>& tl = T.lv[q];
+  if (WAVE && threadIdx.x >= 64) return;
+  Rows M(tl.L, wk, q < T.nord);
+  C *U = sm + tl.off_u, *F = sm + tl.off_f;
+  const C* p = prm + q * T.per;
+  const C *cB = p + 2, *cR = cB + T.KB + 1, *cP = cR + T.KR + 1;
+  const bool pro = (what & (TV_PRO | TV_PRO_SET)) != 0;
+  C f[RPT], u[RPT], x[RPT];
+  TailXfer2<RPT, C> P;
+  if (M.act && pro) P.load(tl.P, M.ic);
+  M.load();
+  if (M.act)
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      f[r] = F[M.ic[r]];
+      u[r] = uz ? C(0) : U[M.ic[r]];
+    }
+  if (!uz) M.store(Rows::V, u);
+  // the restriction's row of this work-item, loaded with the level's rows where registers allow
+  TailXfer8<RPT == 1 || (sizeof(C) == 4 && RPT * W <= 24), C> R;
+  R.load(tl.R, Rows::nt, (what & (TV_RES | TV_RES_F)) != 0);
+  M.zeros();
+  if (!uz) tail_sync<WAVE>();            // the first residual gathers u
+
+  // x = [invdiag] (f - A u)
+  auto resid = [&](int jac) __attribute__((always_inline)) {
+    if (!M.act) return;
+    if (uz) {
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) x[r] = f[r];
+    } else {
+      M.resid(f, u, x);
+    }
+    if (jac)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) x[r] *= M.ida[r];
+  };
+  if (pro) {
+    if (M.act) P.apply(tl.P, M.ic, sm + T.lv[q + 1].off_u, x);
+    M.add(cP, T.KP, C(1), cP[0], (what & TV_PRO_SET) ? 1 : uz, x, u);
+    uz = 0;
+  }
+#pragma nounroll
+  for (int j = 0; j < nsm; ++j) {
+    resid(1);
+    M.add(cB, T.KB, p[0], p[1], uz, x, u);
+    uz = 0;
+  }
+  if (M.act)   // u stays with the level (zero where nothing has been added to it yet)
+#pragma unroll
+    for (int r = 0; r < RPT; ++r)
+      if (M.ok[r]) U[M.ic[r]] = u[r];
+  if (what & (TV_RES | TV_RES_F)) {
+    C v[RPT];
+    if (what & TV_RES) {
+      resid(0);
+    } else if (M.act) {
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) x[r] = f[r];
+    }
+    uint32_t out = Rows::S;
+    if (T.KR == 0) {
+      const C a0 = cR[0];
+      if (M.act)
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) v[r] = tfma(a0, x[r], C(0));
+    } else {
+      out = M.conv(cR, T.KR, x, v);
+    }
+    M.store(out, v);
+    tail_sync<WAVE>();
+    R.apply(tl.R, Rows::nt, wk + out, sm + T.lv[q + 1].off_f);
   }
   tail_sync<WAVE>();
 }
@@ -651,6 +707,23 @@ __device__ __forceinline__ void tail_cycle(const TailArgs<C>& T, C* sm, C* wk, c
   }
 }
 
+// The parameters in the cycle's type to LDS, a level's first two replaced by what the sweeps use: eta
+// theta and (K_B = 0) eta theta c_0; and a small coarsest inverse (per-column operators: the
+// workgroup's column's).
+template <class C>
+__device__ __forceinline__ void tail_params(const TailArgs<C>& T, C* prm, double* inv) {
+  for (int e = threadIdx.x; e < (T.nl - 1) * T.per; e += kTailThreads) {
+    const int k = e % T.per;
+    const double* p = T.prm + (e - k);
+    prm[e] = (C)(k == 0 ? p[1] * p[0] : (k == 1 ? (p[1] * p[0]) * p[2] : p[k]));
+  }
+  if (T.inv_lds) {
+    const Lvl<C>& LJ = T.lv[T.nl - 1].L;
+    const double* Ai = T.Ainv + (LJ.vs ? (size_t)vcol(LJ, (int)blockIdx.x) * T.nJ * T.nJ : 0);
+    for (int e = threadIdx.x; e < T.nJ * T.nJ; e += kTailThreads) inv[e] = Ai[e];
+  }
+}
+
 // fmg == 0: e = LMG(A_lt, f, e) over the tail levels lt .. J-1 (uz: e is zero on entry and not read).
 // fmg == 1: e = FMG(f) over the same levels: f_{q+1} = R Phi_R(f_q), exact
 //           coarsest solve, then per level u_q = Phi_P(P u_{q+1}) and one cycle.
@@ -680,18 +753,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<C> args, int B, 
   };
   load(fg, t0.off_f);
   if (!uz) load(eg, t0.off_u);
-  // the parameters in the cycle's type, a level's first two replaced by what the sweeps use:
-  // eta theta and (K_B = 0) eta theta c_0
-  for (int e = tid; e < (T.nl - 1) * T.per; e += kTailThreads) {
-    const int k = e % T.per;
-    const double* p = T.prm + (e - k);
-    prm[e] = (C)(k == 0 ? p[1] * p[0] : (k == 1 ? (p[1] * p[0]) * p[2] : p[k]));
-  }
-  if (T.inv_lds) {
-    const Lvl<C>& LJ = T.lv[T.nl - 1].L;
-    const double* Ai = T.Ainv + (LJ.vs ? (size_t)vcol(LJ, col) * T.nJ * T.nJ : 0);
-    for (int e = tid; e < T.nJ * T.nJ; e += kTailThreads) inv[e] = Ai[e];
-  }
+  tail_params(T, prm, inv);
   __syncthreads();
   tail_cycle<WG>(T, sm, wk, prm, inv, uz, fmg);
   for (int e = tid; e < t0.L.n; e += kTailThreads) eg[(size_t)e * B + col] = sm[t0.off_u + e];
@@ -701,6 +763,324 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<C> args, int B, 
         T.ckf[q][(size_t)e * B + col] = sm[T.lv[q].off_f + e];
         T.cku[q][(size_t)e * B + col] = sm[T.lv[q].off_u + e];
       }
+  }
+}
+
+// ------------------------------------------------------------------ reverse sweep of the tail
+// The reverse of the cycle over the tail levels for one column per workgroup,
+// from the levels' checkpoint (f_l and the correction u_{l+1} of every level):
+// per level the forward recomputation, the transposed post-smoothing and
+// prolongation (phase 0), then, after the coarser levels, the transposed
+// restriction and pre-smoothing (phase 1), in the order of operations of the
+// per-level sweeps (same bits; only the FP64 parameter dot products sum in
+// another order).  What bounds it is what bounds k_tail: ~45 dependent sweeps a
+// level, where the per-level form paid ~75 launches.  A transposed hop
+// z = G^T y is the neighbour sum of the row-scaled vector, so it reads LDS like a
+// forward hop.  What a level keeps between its phases (S_j, the residual, P e, g
+// and gf) is private to a row and lives in the level's workspace vectors,
+// stored column by column.
+template <class C>
+struct TailBwdLevel {
+  Xfer<C> PT, RT;           // n_{l+1} x n_l and n_l x n_{l+1}
+  C* keep;                  // the level's kept vectors, `stride` apart: S_0 .. S_{nu-1}, residual, P e, g, gf
+  long stride;
+  const C *f, *ec;          // checkpoint: f_l [n_l][B], u_{l+1} [n_{l+1}][B]
+  int slot0, slot1;         // first dot slots of the phases
+};
+template <class C>
+struct TailBwdArgs {
+  TailArgs<C> T;            // off_u / off_f: gradients of a level's output and right-hand side
+  TailBwdLevel<C> b[kTailMaxLevels];
+  int off_dot;              // byte offset in LDS: dot products of a visit per wavefront
+  double* part;             // slot s of column c at s B + c
+};
+
+template <int RPT, int W, bool WAVE, bool SAME, bool VC, bool GC, bool WG, class C>
+__device__ __forceinline__ void tail_bwd_visit(const TailBwdArgs<C>& A, C* sm, uint32_t wk, double* dot, const C* prm,
+                                               int q, int phase, int B, const C* uin, const C* gout, C* gfo, C* gul) {
+  using Rows = TailRows<RPT, W, WAVE, SAME, VC, GC, WG, C>;
+  const TailArgs<C>& T = A.T;
+  const TailLevel<C>& tl = T.lv[q];
+  const TailBwdLevel<C>& tb = A.b[q];
+  if (WAVE && threadIdx.x >= 64) return;
+  Rows M(tl.L, wk, 1);
+  const int n = M.n, col = blockIdx.x, nu = T.nu_pre + T.nu_post, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  C *G = sm + tl.off_u, *GF = sm + tl.off_f;
+  const C* p = prm + q * T.per;
+  const C *cB = p + 2, *cR = cB + T.KB + 1, *cP = cR + T.KR + 1;
+  C g[RPT], gf[RPT], x[RPT], s[RPT];
+  int nd = 0;                      // dot slots of this visit so far
+  auto keep = [&](int k) __attribute__((always_inline)) { return tb.keep + (size_t)k * tb.stride + (size_t)col * n; };
+  auto put = [&](int k, const C (&z)[RPT]) __attribute__((always_inline)) {
+    C* d = keep(k);
+    if (M.act)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r)
+        if (M.ok[r]) d[M.ic[r]] = z[r];
+  };
+  auto get = [&](int k, C (&z)[RPT]) __attribute__((always_inline)) {
+    const C* d = keep(k);
+    if (M.act)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) z[r] = d[M.ic[r]];
+  };
+  auto dots = [&](const C (&z)[RPT]) __attribute__((always_inline)) {
+    double d = 0.0;
+    if (M.act) {
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) d += M.ok[r] ? (double)z[r] * (double)s[r] : 0.0;
+      d = wave_sum(d);
+    }
+    if (lane == 0) dot[nd * 16 + wave] = d;
+    ++nd;
+  };
+  // x <- acc = sum_k c_k (G^T)^k x with the dots <(G^T)^k x, s>; returns the hop buffer that the last
+  // hop does not read
+  auto chain = [&](const C* c, int K) __attribute__((always_inline)) -> uint32_t {
+    C z[RPT];
+    if (M.act)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        z[r] = x[r];
+        x[r] = tfma(c[0], z[r], C(0));
+      }
+    dots(z);
+    auto hopT = [&](uint32_t buf, C ck) __attribute__((always_inline)) {
+      C t[RPT];
+      if (M.act)
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) t[r] = z[r] * M.idg[r];
+      M.store(buf, t);
+      tail_sync<WAVE>();
+      if (M.act) {
+        M.gsum(buf, z);
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) x[r] = tfma(ck, z[r], x[r]);
+      }
+      dots(z);
+    };
+    int k = 1;
+#pragma nounroll
+    for (; k + 1 <= K; k += 2) {
+      hopT(Rows::S, c[k]);
+      hopT(Rows::Y, c[k + 1]);
+    }
+    if (k > K) return Rows::S;
+    hopT(Rows::S, c[k]);
+    return Rows::Y;
+  };
+  // q = alpha acc [invdiag], gf += q, g -= A q
+  auto apply = [&](C alpha, int jac, bool first) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+    if (M.act)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        C v = alpha * x[r];
+        if (jac) v *= M.ida[r];
+        x[r] = v;
+        gf[r] = first ? v : gf[r] + v;
+      }
+    M.store(Rows::V, x);
+    tail_sync<WAVE>();
+    if (M.act) {
+      C t[RPT];
+      M.resid(g, x, t);
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) g[r] = t[r];
+    }
+  };
+  auto smoothT = [&](int j, bool first) __attribute__((always_inline)) {
+    if (T.KB == 0) tail_sync<WAVE>();   // (a convolution's barriers otherwise end the reads of the last A q)
+    get(j, s);
+    if (M.act)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) x[r] = g[r];
+    chain(cB, T.KB);
+    apply(p[0], 1, first);
+  };
+
+  if (phase == 0) {
+    TailXfer2<RPT, C> P;
+    if (M.act) P.load(tl.P, M.ic);
+    M.load();
+    C f[RPT], u[RPT];
+    int uz = 1;
+    if (M.act)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        f[r] = tb.f[(size_t)M.ic[r] * B + col];
+        u[r] = C(0);
+      }
+    if (q == 0 && uin) {
+      uz = 0;
+      if (M.act)
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) u[r] = uin[(size_t)M.ic[r] * B + col];
+      M.store(Rows::V, u);
+    }
+    // the correction e_{l+1} to LDS (the next level's gf, not in use yet)
+    C* E = sm + T.lv[q + 1].off_f;
+    const int nc = T.lv[q + 1].L.n;
+    for (int e = threadIdx.x; e < nc; e += Rows::nt) E[e] = tb.ec[(size_t)e * B + col];
+    M.zeros();
+    tail_sync<WAVE>();
+    auto resid = [&](int jac) __attribute__((always_inline)) {
+      if (!M.act) return;
+      if (uz) {
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) x[r] = f[r];
+      } else {
+        M.resid(f, u, x);
+      }
+      if (jac)
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) x[r] *= M.ida[r];
+    };
+    // forward recomputation; the iterate after the last step is not needed
+#pragma nounroll
+    for (int j = 0; j < T.nu_pre; ++j) {
+      resid(1);
+      put(j, x);
+      M.add(cB, T.KB, p[0], p[1], uz, x, u);
+      uz = 0;
+    }
+    resid(0);
+    put(nu, x);
+    if (M.act) P.apply(tl.P, M.ic, E, x);
+    put(nu + 1, x);
+    if (T.nu_post) M.add(cP, T.KP, C(1), cP[0], uz, x, u);
+    uz = 0;
+#pragma nounroll
+    for (int j = 0; j < T.nu_post; ++j) {
+      resid(1);
+      put(T.nu_pre + j, x);
+      if (j + 1 < T.nu_post) M.add(cB, T.KB, p[0], p[1], 0, x, u);
+    }
+    // reverse
+    if (M.act)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        g[r] = q == 0 ? gout[(size_t)M.ic[r] * B + col] : G[M.ic[r]];
+        gf[r] = C(0);
+      }
+    tail_sync<WAVE>();             // the work buffers change hands
+#pragma nounroll
+    for (int j = T.nu_post - 1; j >= 0; --j) smoothT(T.nu_pre + j, j == T.nu_post - 1);
+    get(nu + 1, s);
+    if (M.act)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) x[r] = g[r];
+    const uint32_t out = chain(cP, T.KP);
+    M.store(out, x);
+    put(nu + 2, g);
+    put(nu + 3, gf);
+    tail_sync<WAVE>();
+    TailXfer8<false, C> R;
+    R.load(tb.PT, Rows::nt, false);
+    R.apply(tb.PT, Rows::nt, wk + out, sm + T.lv[q + 1].off_u);
+  } else {
+    TailXfer2<RPT, C> P;
+    if (M.act) P.load(tb.RT, M.ic);
+    M.load();
+    get(nu + 2, g);
+    get(nu + 3, gf);
+    M.zeros();
+    if (M.act) P.apply(tb.RT, M.ic, sm + T.lv[q + 1].off_f, x);
+    get(nu, s);
+    chain(cR, T.KR);
+    apply(C(1), 0, T.nu_post == 0);
+#pragma nounroll
+    for (int j = T.nu_pre - 1; j >= 0; --j) smoothT(j, false);
+    if (M.act)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        if (!M.ok[r]) continue;
+        if (q == 0) {
+          gfo[(size_t)M.ic[r] * B + col] = gf[r];
+          if (gul) gul[(size_t)M.ic[r] * B + col] = g[r];
+        } else {
+          GF[M.ic[r]] = gf[r];
+        }
+      }
+  }
+  tail_sync<WAVE>();
+  // the visit's dot products over the wavefronts, in order
+  for (int t = threadIdx.x; t < nd; t += Rows::nt) {
+    double d = 0.0;
+    for (int w = 0; w < Rows::nt / 64; ++w) d += dot[t * 16 + w];
+    A.part[(size_t)((phase ? tb.slot1 : tb.slot0) + t) * B + col] = d;
+  }
+  tail_sync<WAVE>();
+}
+
+template <bool WG, class C>
+__device__ __forceinline__ void tail_bwd_level(const TailBwdArgs<C>& A, C* sm, C* wk, double* dot, const C* prm, int q,
+                                               int phase, int B, const C* uin, const C* gout, C* gfo, C* gul) {
+  const int rpt = A.T.lv[q].rpt, w = A.T.lv[q].w;
+  const uint32_t wa = lds_addr(wk);
+  constexpr bool F32 = sizeof(C) == 4;
+#define MGL_TB(R, W_, WAVE, SAME, VC, GC) \
+  tail_bwd_visit<R, W_, WAVE, SAME, VC, GC, WG, C>(A, sm, wa, dot, prm, q, phase, B, uin, gout, gfo, gul)
+#define MGL_TBW(R, VC, GC)                               \
+  do {                                                   \
+    if (w <= 6) MGL_TB(R, 6, false, true, VC, GC);       \
+    else if (w <= 8) MGL_TB(R, 8, false, true, VC, GC);  \
+    else MGL_TB(R, 8, false, false, VC, GC);             \
+  } while (0)
+  if (A.T.lv[q].L.n <= 64) {
+    if (w <= 6) MGL_TB(1, 6, true, true, true, true);
+    else MGL_TB(1, 8, true, false, true, true);
+    __syncthreads();
+  } else if (rpt == 1) {
+    MGL_TBW(1, true, true);
+  } else if (rpt == 2) {
+    if constexpr (F32) MGL_TBW(2, true, false);
+    else MGL_TBW(2, false, false);
+  } else {
+    if constexpr (F32) MGL_TBW(4, true, false);
+  }
+#undef MGL_TBW
+#undef MGL_TB
+}
+// rows per work-item of a level in the reverse sweep (0: not in it)
+template <class C> constexpr int tail_bwd_rpt(int rpt) {
+  return sizeof(C) == 4 ? (rpt == 3 ? 4 : rpt) : (rpt <= 2 ? rpt : 0);
+}
+
+template <bool WG, class C>
+__global__ __launch_bounds__(kTailThreads) void k_tail_bwd(TailBwdArgs<C> args, int B, const C* __restrict__ uin,
+                                                           const C* __restrict__ gout, C* __restrict__ gfo,
+                                                           C* __restrict__ gul) {
+  extern __shared__ __align__(16) unsigned char tail_smem[];
+  const TailBwdArgs<C>& A = *(const TailBwdArgs<C>*)__builtin_amdgcn_kernarg_segment_ptr();   // (as in k_tail)
+  const TailArgs<C>& T = A.T;
+  C* sm = reinterpret_cast<C*>(tail_smem + T.off_vec);
+  C* wk = reinterpret_cast<C*>(tail_smem + T.off_wk);
+  C* prm = reinterpret_cast<C*>(tail_smem + T.off_prm);
+  double* inv = reinterpret_cast<double*>(tail_smem + T.off_inv);
+  double* dot = reinterpret_cast<double*>(tail_smem + A.off_dot);
+  tail_params(T, prm, inv);
+  __syncthreads();
+  const int last = T.nl - 1;
+  int phase = 0, q = 0;
+#pragma nounroll
+  while (q >= 0) {
+    if (q == last) {
+      // gf = A^{-T} g
+      const TailLevel<C>& tl = T.lv[last];
+      const double* Ai = T.inv_lds ? nullptr : T.Ainv;
+      for (int i = threadIdx.x; i < T.nJ; i += kTailThreads) {
+        double acc = 0.0;
+        for (int j = 0; j < T.nJ; ++j)
+          acc = __builtin_fma(Ai ? Ai[(size_t)j * T.nJ + i] : inv[j * T.nJ + i], (double)sm[tl.off_u + j], acc);
+        sm[tl.off_f + i] = (C)acc;
+      }
+      __syncthreads();
+      phase = 1;
+      q = last - 1;
+    }
+    tail_bwd_level<WG>(A, sm, wk, dot, prm, q, phase, B, uin, gout, gfo, gul);
+    q += phase ? -1 : 1;
   }
 }
 
