@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "chebtab.hpp"
+#include "lanes.hpp"
 
 namespace mgl {
 
@@ -1265,63 +1266,270 @@ __global__ __launch_bounds__(256) void k_fill0(long cnt, T* out) {
 }
 
 // ------------------------------------------------------------------ adjoint sweeps
-// Block-wide FP64 sum, written to part[blockIdx.x] (deterministic tree).
-__device__ __forceinline__ void block_sum_store(double v, double* part, double* red) {
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+// Block-wide sum (four wavefronts) of each of N values, value k to part[k * stride + blockIdx.x].
+template <int N>
+__device__ __forceinline__ void block_sum_store(const Sum2 (&v)[N], Sum2* part, long stride) {
+  __shared__ Sum2 red[4 * N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const Sum2 w = wave_sum(v[k]);
+    if ((threadIdx.x & 63) == 0) red[4 * k + (threadIdx.x >> 6)] = w;
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  __syncthreads();
+  if ((int)threadIdx.x < N) {
+    const Sum2* r = red + 4 * threadIdx.x;
+    part[(size_t)threadIdx.x * stride + blockIdx.x] = sum2_add(sum2_add(r[0], r[1]), sum2_add(r[2], r[3]));
+  }
 }
 
-// One power step of a transposed convolution:
-//   zin == nullptr: z = zsrc (k = 0);  else z = M^T zin
-//   acc = (first ? 0 : acc) + c * z;  zout = z (if zout);  part <- sum(z * s)
+// What becomes of a transposed convolution's sum acc (the last sweep of its chain):
+//   fin 0: acc is stored      fin 1: q = alpha acc [invdiag], gf = (gz ? 0 : gf) + q (gf optional)
+struct ChainEnd {
+  int fin, jacobi, gz;
+};
+template <class C>
+__device__ __forceinline__ C chain_q(C alpha, C acc, int jacobi, C invdiag) {
+#pragma clang fp contract(off)
+  const C v = alpha * acc;
+  return jacobi ? v * invdiag : v;
+}
+
+// One or two power steps of a transposed convolution sum_k c_k (M^T)^k z_0:
+//   FIRST: z_0 = zin's own row, acc = c0 z_0 and part <- sum(z_0 s); else acc is read
+//   HOP:   z = M^T zin, acc += c z, part (the next slot after FIRST's) <- sum(z s), zout = z (if zout)
+//   LAST:  acc ends as ChainEnd says, else it is stored
+// A chain of K >= 1 hops is K launches (the first with k = 0 and 1), and its scaling, the sum
+// into gf and the store of acc need none of their own: the sweeps are bandwidth bound on fine levels
+// (14 us a hop on 255 x 255 x 32) and launches on coarse ones.
 // Every work-item reaches the block sum (no early return).
-template <int ROWS, bool WIDE, bool WG, class C, class TZ, class TS>
+template <int ROWS, bool WIDE, bool WG, bool FIRST, bool HOP, bool LAST, class C, class TZ, class TS>
 __global__ __launch_bounds__(256) void k_hopT(Lvl<C> L, int B, int lbs, const TZ* __restrict__ zin,
-                                              const TZ* __restrict__ zsrc, TZ* __restrict__ zout, C c,
-                                              TZ* __restrict__ acc, int first, const TS* __restrict__ s,
-                                              double* __restrict__ part) {
-  __shared__ double red[256];
+                                              TZ* __restrict__ zout, C c0, C c, TZ* __restrict__ acc,
+                                              const TS* __restrict__ s, Sum2* __restrict__ part, long pstride,
+                                              ChainEnd end, C alpha, TZ* __restrict__ q, TZ* gf) {
   const Tile<ROWS, WIDE> t(L.n, lbs);
-  double d = 0.0;
+  Sum2 d[(FIRST ? 1 : 0) + (HOP ? 1 : 0)] = {};
   for (int b = t.lane; b < B; b += t.LB) {
     C z[ROWS], av[ROWS], sv[ROWS];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
       const size_t o = (size_t)t.row[r] * B + b;
-      z[r] = zin ? C(0) : ldc<C>(zsrc + o);
-      av[r] = first ? C(0) : ldc<C>(acc + o);
       sv[r] = ldc<C>(s + o);
+      if constexpr (FIRST) {
+        const C z0 = ldc<C>(zin + o);
+        av[r] = c0 * z0;
+        if (t.ok[r]) d[0] = sum2_add(d[0], (double)z0 * (double)sv[r]);
+      } else {
+        av[r] = ldc<C>(acc + o);
+      }
+      z[r] = C(0);
     }
-    if (zin) graph_sum<WIDE, false, ROWS, true, WG>(L, t.row, t.row0, zin, B, b, z);
+    if constexpr (HOP) graph_sum<WIDE, false, ROWS, true, WG>(L, t.row, t.row0, zin, B, b, z);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
       if (!t.ok[r]) continue;
       const size_t o = (size_t)t.row[r] * B + b;
-      if (zout) put(zout + o, z[r]);
-      put(acc + o, av[r] + c * z[r]);
-      d += (double)z[r] * (double)sv[r];
+      if constexpr (HOP) {
+        if (zout) put(zout + o, z[r]);
+        av[r] = hop_update(av[r], c, z[r]);
+        d[FIRST ? 1 : 0] = sum2_add(d[FIRST ? 1 : 0], (double)z[r] * (double)sv[r]);
+      }
+      if (!LAST || end.fin == 0) {
+        put(acc + o, av[r]);
+      } else {
+        const C v = chain_q(alpha, av[r], end.jacobi, end.jacobi ? L.invdiag[t.row[r]] : C(1));
+        put(q + o, v);
+        if (gf) put(gf + o, (end.gz ? C(0) : ldc<C>(gf + o)) + v);
+      }
     }
   }
-  block_sum_store(d, part, red);
+  block_sum_store(d, part, pstride);
 }
 
-// Tail of a transposed smoothing / residual step:
-//   q = alpha * [invdiag *] acc;  gf = (gz ? 0 : gf) + q  (gf optional)
-template <class C, class TZ>
-__global__ __launch_bounds__(256) void k_scale_acc(Lvl<C> L, int B, int lbs, const TZ* __restrict__ acc,
-                                                   C alpha, int jacobi, TZ* __restrict__ q, TZ* gf, int gz) {
-  MGL_ROW_LANE(L.n)
-  for (int b = lane; b < B; b += (1 << lbs)) {
-    const size_t o = (size_t)i * B + b;
-    C v = alpha * ldc<C>(acc + o);
-    if (jacobi) v *= L.invdiag[i];
-    put(q + o, v);
-    if (gf) put(gf + o, (gz ? C(0) : ldc<C>(gf + o)) + v);
+// The whole chain of a transposed convolution of K >= 2 hops over tiles (FP32): as k_conv_tile, with
+// the row scale applied as rows enter LDS (a transposed hop sums r_j z_j), the sum acc of the own
+// nodes in registers and their dot products with s, slot k of this block at
+// part[k * gridDim.x + blockIdx.x].  What bounds it is what bounds k_conv_tile (the LDS gathers; four
+// wavefronts a SIMD hide the prefetch): 14.5 us with K = 3, the mean over levels of 255 x 255 and
+// 127 x 127 x 32; the four hops' sweeps and the scaling's took 62 on the finer of them alone.
+template <bool WG, class TS>
+__global__ __launch_bounds__(kTileThreads, 4) void k_chain_tile(TileDev T, int B, int K, TileCoef cf,
+                                                            const float* __restrict__ x,
+                                                            const float* __restrict__ invdeg,
+                                                            const TS* __restrict__ s, float* __restrict__ out,
+                                                            ChainEnd end, float alpha,
+                                                            const float* __restrict__ invdiag, float* gf,
+                                                            Sum2* __restrict__ part, TileLds lo) {
+  extern __shared__ __align__(16) float4 conv_smem[];
+  const int per = gridDim.x >> 3;             // workgroups per XCD
+  const int xc = blockIdx.x & 7;
+  const int W = T.ntiles * T.ngroups;
+  const int i1 = (int)((long long)W * (xc + 1) / 8);
+  int it = (int)((long long)W * xc / 8) + (blockIdx.x >> 3);
+  if (it >= i1) {
+    if ((int)threadIdx.x <= K) part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = Sum2{0.0, 0.0};
+    return;
+  }
+  const int q = threadIdx.x % kTileQ;
+  const int p0 = threadIdx.x / kTileQ;
+  const int KM = T.KM, wg = T.wg, lane = threadIdx.x & 63;
+  float4* S = conv_smem + lo.xs;
+  for (int z = threadIdx.x; z < 3 * kTileQ; z += blockDim.x) {   // the rows of zeros before the buffers
+    const int base = z < kTileQ ? lo.xs : (z < 2 * kTileQ ? lo.y0 : lo.y1);
+    conv_smem[base - kTileQ + z % kTileQ] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  uint2* LC2 = reinterpret_cast<uint2*>(conv_smem + lo.col);
+  const uint16_t* LC = reinterpret_cast<const uint16_t*>(conv_smem + lo.col);
+  float* LI = reinterpret_cast<float*>(conv_smem + lo.idg);
+  Sum2 dsum{0.0, 0.0};                        // lane k: this wavefront's dot product k
+
+  auto head = [&](int i, TileHead& h) {
+    h.t = i / T.ngroups;
+    h.g = i - h.t * T.ngroups;
+    const int* cn = T.cnt + (size_t)h.t * (KM + 1);
+    h.cK = ld_const(cn + K);
+    h.rows1 = ld_const(cn + K - 1);
+    h.own = ld_const(cn);
+    h.base = ld_const(T.toff + h.t);
+    h.m0 = ld_const(T.goff + h.t);
+#pragma unroll
+    for (int e = 0; e < kTileRows; ++e) h.nd[e] = T.node[h.base + min(p0 + e * kTileNp, h.cK - 1)];
+  };
+  // prefetched: the input rows, their scales, the own rows' s (in ov), the columns and row scales
+  auto body = [&](const TileHead& h, TileBody& b) {
+    const int col = h.g * kTileCols + q * 4;
+#pragma unroll
+    for (int e = 0; e < kTileRows; ++e) {
+      ld4v(x + (size_t)h.nd[e] * B + col, b.xv[e]);
+      b.xs[e] = invdeg[h.nd[e]];
+    }
+#pragma unroll
+    for (int e = 0; e < kTileOwnPerThread; ++e) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) b.ov[e][c] = 0.f;
+      if (p0 + e * kTileNp < h.own) ld4v(s + (size_t)h.nd[e] * B + col, b.ov[e]);
+    }
+    const uint2* src = reinterpret_cast<const uint2*>(T.lcol + h.m0);
+    const float* ls = T.lidg + h.m0 / wg;
+    const int nch = h.rows1 * wg / 4;
+#pragma unroll
+    for (int e = 0; e < kTileMeta; ++e) {
+      const int c = threadIdx.x + e * kTileThreads;
+      if (c < nch) b.lc[e] = src[c];
+      if (c < h.rows1) b.li[e] = ls[c];
+    }
+  };
+
+  TileHead hc, hn;
+  TileBody bc;
+  head(it, hc);
+  body(hc, bc);
+  int itn = it + per;
+  if (itn < i1) head(itn, hn);
+  while (true) {
+    const TileHead h = hc;
+    float sv[kTileOwnPerThread][4], acc[kTileOwnPerThread][4];
+    Sum2 d{0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < kTileOwnPerThread; ++e)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        sv[e][c] = bc.ov[e][c];               // zero on rows that are not the tile's own
+        acc[e][c] = cf.c[0] * bc.xv[e][c];
+        d = sum2_add(d, (double)bc.xv[e][c] * (double)sv[e][c]);
+      }
+#pragma unroll
+    for (int e = 0; e < kTileRows; ++e) {
+      const int r = p0 + e * kTileNp;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) bc.xv[e][c] *= bc.xs[e];
+      if (r < h.cK) S[r * kTileQ + q] = make_float4(bc.xv[e][0], bc.xv[e][1], bc.xv[e][2], bc.xv[e][3]);
+    }
+    {
+      const int nch = h.rows1 * wg / 4;
+#pragma unroll
+      for (int e = 0; e < kTileMeta; ++e) {
+        const int c = threadIdx.x + e * kTileThreads;
+        if (c < nch) LC2[c] = bc.lc[e];
+        if (c < h.rows1) LI[c] = bc.li[e];
+      }
+    }
+    __syncthreads();
+    const bool more = itn < i1;
+    if (more) {
+      body(hn, bc);
+      hc = hn;
+    }
+    const int itnn = itn + per;
+    if (itnn < i1) head(itnn, hn);
+    d = wave_sum(d);
+    if (lane == 0) dsum = sum2_add(dsum, d);
+    const int* cn = T.cnt + (size_t)h.t * (KM + 1);
+    const float* gw = WG ? T.lgw + h.m0 : nullptr;
+    const float4* yin = S - kTileQ;
+    for (int hp = 1; hp <= K; ++hp) {
+      const int rows = ld_const(cn + K - hp);
+      const float ck = cf.c[hp];
+      float4* yo = conv_smem + ((hp & 1) ? lo.y0 : lo.y1);
+      d = Sum2{0.0, 0.0};
+#pragma unroll
+      for (int e = 0; e < kTileRows; ++e) {
+        const int r = p0 + e * kTileNp;
+        if (r < rows) {
+          float z[4] = {0.f, 0.f, 0.f, 0.f};
+          tile_gather<WG>(wg, LC + r * wg, WG ? gw + (size_t)r * wg : nullptr, yin, q, z);
+          if (e < kTileOwnPerThread) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              acc[e][c] = hop_update(acc[e][c], ck, z[c]);
+              d = sum2_add(d, (double)z[c] * (double)sv[e][c]);
+            }
+          }
+          if (hp < K) {
+            const float ri = LI[r];
+            yo[r * kTileQ + q] = make_float4(z[0] * ri, z[1] * ri, z[2] * ri, z[3] * ri);
+          }
+        }
+      }
+      d = wave_sum(d);
+      if (lane == hp) dsum = sum2_add(dsum, d);
+      __syncthreads();
+      yin = yo - kTileQ;
+    }
+    const int col = h.g * kTileCols + q * 4;
+#pragma unroll
+    for (int e = 0; e < kTileOwnPerThread; ++e) {
+      if (p0 + e * kTileNp >= h.own) continue;
+      const size_t o = (size_t)h.nd[e] * B + col;
+      if (end.fin == 0) {
+        st4v(out + o, acc[e]);
+      } else {
+        const float id = end.jacobi ? invdiag[h.nd[e]] : 1.f;
+        float v[4], g[4] = {0.f, 0.f, 0.f, 0.f};
+        if (gf && !end.gz) ld4v(gf + o, g);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          v[c] = chain_q(alpha, acc[e][c], end.jacobi, id);
+          g[c] += v[c];
+        }
+        st4v(out + o, v);
+        if (gf) st4v(gf + o, g);
+      }
+    }
+    if (!more) break;
+    it = itn;
+    itn = itnn;
+  }
+  // (the last hop's barrier ended every read of the buffers)
+  Sum2* red = reinterpret_cast<Sum2*>(conv_smem);
+  constexpr int NW = kTileThreads / 64;
+  if (lane <= K) red[(threadIdx.x >> 6) * (kTileMaxK + 1) + lane] = dsum;
+  __syncthreads();
+  if ((int)threadIdx.x <= K) {
+    Sum2 v{0.0, 0.0};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) v = sum2_add(v, red[w * (kTileMaxK + 1) + threadIdx.x]);
+    part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = v;
   }
 }
 
@@ -1345,49 +1553,51 @@ __global__ __launch_bounds__(256) void k_sub_Aq(Lvl<C> L, int B, int lbs, const 
   }
 }
 
-// dots[s] = sum_{g < cnt[s]} part[off[s] + g]
-__global__ void k_dots_final(const double* __restrict__ part, const long* __restrict__ off,
-                             const int* __restrict__ cnt, int nslots, double* __restrict__ dots) {
-  __shared__ double red[256];
+// dots[s] = sum_{g < cnt[s]} part[off[s] + g], rounded here
+__global__ __launch_bounds__(256) void k_dots_final(const Sum2* __restrict__ part, const long* __restrict__ off,
+                                                    const int* __restrict__ cnt, int nslots,
+                                                    double* __restrict__ dots) {
+  __shared__ Sum2 red[4];
   const int s = blockIdx.x;
   if (s >= nslots) return;
-  double v = 0.0;
-  for (int g = threadIdx.x; g < cnt[s]; g += blockDim.x) v += part[off[s] + g];
-  red[threadIdx.x] = v;
+  Sum2 v{0.0, 0.0};
+  for (int g = threadIdx.x; g < cnt[s]; g += blockDim.x) v = sum2_add(v, part[off[s] + g]);
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int k = blockDim.x / 2; k > 0; k >>= 1) {
-    if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    v = sum2_add(sum2_add(red[0], red[1]), sum2_add(red[2], red[3]));
+    dots[s] = v.hi + v.lo;
   }
-  if (threadIdx.x == 0) dots[s] = red[0];
 }
 
-// Parameter gradients from the dot products, in a fixed order.
+// Parameter gradients from the dot products: one work-item per parameter, each adding the slots that
+// belong to it in slot order (12 us at 150 slots; one work-item adding all of them took 61).
 // desc[s] = {kind (0 smoother, 1 restriction, 2 prolongation), level, k}.
 // Smoother dot e = <(M^T)^k g, s> with s = D^{-1}(f - A u):
 //   dc_k += eta theta e,  deta += theta c_k e,  dtheta += eta c_k e.
 // Transfer dots give dc_k directly.
-__global__ void k_grad_combine(const double* __restrict__ dots, const int* __restrict__ desc, int nslots,
-                               const double* __restrict__ prm, int per, int KB, int KR, double* __restrict__ g,
-                               int np) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  for (int t = 0; t < np; ++t) g[t] = 0.0;
-  for (int s = 0; s < nslots; ++s) {
-    const int kind = desc[3 * s], l = desc[3 * s + 1], k = desc[3 * s + 2];
-    const double* p = prm + (size_t)l * per;
-    double* gl = g + (size_t)l * per;
-    const double e = dots[s];
-    if (kind == 0) {
-      const double th = p[0], et = p[1], ck = p[2 + k];
-      gl[2 + k] += et * th * e;
-      gl[1] += th * ck * e;
-      gl[0] += et * ck * e;
-    } else if (kind == 1) {
-      gl[2 + KB + 1 + k] += e;
-    } else {
-      gl[2 + KB + 1 + KR + 1 + k] += e;
-    }
+__global__ __launch_bounds__(256) void k_grad_combine(const double* __restrict__ dots, const int* __restrict__ desc,
+                                                      int nslots, const double* __restrict__ prm, int per, int KB,
+                                                      int KR, double* __restrict__ g, int np) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= np) return;
+  const int l = t / per, o = t - l * per;
+  const double* p = prm + (size_t)l * per;
+  const double th = p[0], et = p[1];
+  double v = 0.0;
+#pragma unroll 8
+  for (int s = 0; s < nslots; ++s) {          // no branch around the loads: eight slots' are in flight
+    const int kind = desc[3 * s], ls = desc[3 * s + 1], k = desc[3 * s + 2];
+    const double e = dots[s], ck = p[2 + (kind == 0 ? k : 0)];
+    const bool own = kind == 0 ? o == 2 + k : o == 2 + KB + 1 + (kind == 1 ? 0 : KR + 1) + k;
+    double w = 0.0;
+    w = kind == 0 && o == 0 ? et * ck * e : w;
+    w = kind == 0 && o == 1 ? th * ck * e : w;
+    w = own ? (kind == 0 ? et * th * e : e) : w;
+    v += ls == l ? w : 0.0;
   }
+  g[t] = v;
 }
 
 // Gradients with respect to Chebyshev coefficients from those with respect to

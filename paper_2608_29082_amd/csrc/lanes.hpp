@@ -45,4 +45,49 @@ __device__ __forceinline__ double wave_sum(double v) {
   return lane_add32(lane_add16(v));
 }
 
+// An unevaluated sum hi + lo of two doubles: sums of products kept this way round once, at the end, to
+// about twice the FP64 precision, so they do not depend on the order of their terms (the same bits from
+// sweeps that walk rows, tiles or columns).
+struct Sum2 {
+  double hi, lo;
+};
+// s + v (Knuth's two-sum; the error of hi goes to lo)
+__device__ __forceinline__ Sum2 sum2_add(Sum2 s, double v) {
+  const double h = s.hi + v, t = h - s.hi;
+  return Sum2{h, s.lo + ((s.hi - (h - t)) + (v - t))};
+}
+__device__ __forceinline__ Sum2 sum2_add(Sum2 a, Sum2 b) {
+  Sum2 s = sum2_add(a, b.hi);
+  s.lo += b.lo;
+  return s;
+}
+template <int CTRL>
+__device__ __forceinline__ Sum2 lane_dpp(Sum2 v) {
+  return Sum2{lane_dpp<CTRL>(v.hi), lane_dpp<CTRL>(v.lo)};
+}
+// the pair of values 16 (32) lanes apart, as (one, other) in both lanes
+__device__ __forceinline__ Sum2 lane_sum16(Sum2 v) {
+  const long long h = __double_as_longlong(v.hi), l = __double_as_longlong(v.lo);
+  const auto a = __builtin_amdgcn_permlane16_swap((unsigned)h, (unsigned)h, false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap((unsigned)(h >> 32), (unsigned)(h >> 32), false, false);
+  const auto c = __builtin_amdgcn_permlane16_swap((unsigned)l, (unsigned)l, false, false);
+  const auto d = __builtin_amdgcn_permlane16_swap((unsigned)(l >> 32), (unsigned)(l >> 32), false, false);
+  return sum2_add(Sum2{lane_pair(a[0], b[0]), lane_pair(c[0], d[0])}, Sum2{lane_pair(a[1], b[1]), lane_pair(c[1], d[1])});
+}
+__device__ __forceinline__ Sum2 lane_sum32(Sum2 v) {
+  const long long h = __double_as_longlong(v.hi), l = __double_as_longlong(v.lo);
+  const auto a = __builtin_amdgcn_permlane32_swap((unsigned)h, (unsigned)h, false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap((unsigned)(h >> 32), (unsigned)(h >> 32), false, false);
+  const auto c = __builtin_amdgcn_permlane32_swap((unsigned)l, (unsigned)l, false, false);
+  const auto d = __builtin_amdgcn_permlane32_swap((unsigned)(l >> 32), (unsigned)(l >> 32), false, false);
+  return sum2_add(Sum2{lane_pair(a[0], b[0]), lane_pair(c[0], d[0])}, Sum2{lane_pair(a[1], b[1]), lane_pair(c[1], d[1])});
+}
+__device__ __forceinline__ Sum2 wave_sum(Sum2 v) {
+  v = sum2_add(v, lane_dpp<kDppXor1>(v));
+  v = sum2_add(v, lane_dpp<kDppXor2>(v));
+  v = sum2_add(v, lane_dpp<kDppHalfMirror>(v));
+  v = sum2_add(v, lane_dpp<kDppRor8>(v));
+  return lane_sum32(lane_sum16(v));
+}
+
 }  // namespace mgl

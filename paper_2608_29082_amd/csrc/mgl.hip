@@ -230,7 +230,8 @@ struct Engine final : EngineBase {
   double *part = nullptr, *norms = nullptr, *fnorm = nullptr, *init = nullptr;
   double *lalpha = nullptr, *lbeta = nullptr;   // residual-loss gradient coefficients per column
   int* dstat = nullptr;
-  double *dots = nullptr, *dpart = nullptr, *dprm = nullptr;
+  double *dots = nullptr, *dprm = nullptr;
+  Sum2* dpart = nullptr;            // reverse sweep: partial dot products per slot
   long* doff = nullptr;
   int *dcnt = nullptr, *ddesc = nullptr;
   int nslots = 0;
@@ -287,12 +288,17 @@ struct Engine final : EngineBase {
   const double* cP(int l) const { return cR(l) + pl.KR + 1; }
 
   // slots of the reverse sweep, in launch order (kind, level, k): a slot's partial sums are one per
-  // block of the level's sweeps, or one per column in the tail (most: the larger of both, for sizes)
+  // block of the level's sweeps (row sweeps or tiles), or one per column in the tail (most: the largest
+  // of these, for sizes)
   void enum_slots(int l, bool most) {
     const int J = pl.J;
     if (l == J - 1) return;
-    const int rb = (int)d[l].rblocks, cnt = most ? std::max(rb, pl.B) : (btail_lt >= 0 && l >= btail_lt ? pl.B : rb);
+    const int rb = (int)d[l].rblocks;
     auto add = [&](int kind, int K) {
+      int cnt = rb;
+      if (most) cnt = std::max({rb, pl.B, pl.lv[l].n >= kTileMinRows ? (int)kChainBlocks : 0});
+      else if (btail_lt >= 0 && l >= btail_lt) cnt = pl.B;
+      else if (chain_tiled(l, K)) cnt = (int)chain_grid(l, K);
       for (int k = 0; k <= K; ++k) {
         h_desc.push_back(kind); h_desc.push_back(l); h_desc.push_back(k);
         h_cnt.push_back(cnt);
@@ -442,7 +448,7 @@ struct Engine final : EngineBase {
       enum_slots(0, true);
       nslots = (int)h_cnt.size();
       const long tot = nslots ? h_off.back() + h_cnt.back() : 0;
-      dpart = bp.take<double>(tot);
+      dpart = bp.take<Sum2>(tot);
       dots = bp.take<double>(nslots);
       doff = bp.take<long>(nslots);
       dcnt = bp.take<int>(nslots);
@@ -739,7 +745,7 @@ struct Engine final : EngineBase {
     int dev = 0, maxlds = 0;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-    const size_t dots = (size_t)std::max(slots_down(), slots_up()) * 16 * sizeof(double);
+    const size_t dots = (size_t)std::max(slots_down(), slots_up()) * 16 * sizeof(Sum2);
     TailBwdArgs<C> a{};
     size_t bytes = 0;
     int lt = J - 1;
@@ -813,6 +819,7 @@ struct Engine final : EngineBase {
 #define MGL_TILE_MIN_ROWS 2048
 #endif
   static constexpr int kTileMinRows = MGL_TILE_MIN_ROWS;
+  static constexpr unsigned kChainBlocks = 1024;   // blocks of a transposed convolution over tiles (at most)
   static constexpr size_t kTileLds = MGL_TILE_LDS_KB * 1024;
   mg_status setup_tiles(hipStream_t st) {
     if constexpr (std::is_same<C, float>::value) return setup_tiles_f(st);
@@ -910,6 +917,13 @@ struct Engine final : EngineBase {
         reinterpret_cast<const void*>(&k_conv_tile<true, true, TH, TU>),
         reinterpret_cast<const void*>(&k_conv_tile<true, false, TU, TH>),
         reinterpret_cast<const void*>(&k_conv_tile<true, true, TU, TH>)};
+    const void* cfns[] = {reinterpret_cast<const void*>(&k_chain_tile<false, TH>),
+                          reinterpret_cast<const void*>(&k_chain_tile<true, TH>),
+                          reinterpret_cast<const void*>(&k_chain_tile<false, TU>),
+                          reinterpret_cast<const void*>(&k_chain_tile<true, TU>)};
+    if (maxlds > 65536 && bwd())
+      for (const void* fn : cfns)
+        HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)maxlds));
     if (maxlds > 65536)
       for (const void* fn : fns)
         HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)maxlds));
@@ -1738,41 +1752,62 @@ struct Engine final : EngineBase {
   // ---------------------------------------------------------------- reverse sweep
   int slot = 0;
 
-  // z_0 = src, z_k = M^T z_{k-1};  acc = sum_k c_k z_k;  dot slots <z_k, sdot>
-  mg_status chainT(int l, const double* c, int K, const TU* src, const void* sdot, bool sdot_is_TH, hipStream_t st) {
+  // whether a transposed convolution of order K on level l runs as one launch over tiles
+  bool chain_tiled(int l, int K) const {
+    return std::is_same<C, float>::value && d[l].td.ntiles > 0 && K >= 2 && K <= d[l].td.KM;
+  }
+  unsigned chain_grid(int l, int K) const { return std::min(d[l].tgrid[K], kChainBlocks); }
+
+  // z_0 = src, z_k = M^T z_{k-1};  acc = sum_k c_k z_k;  dot slots <z_k, sdot>; then acc goes to D.acc
+  // (end.fin 0) or becomes D.q = alpha acc [invdiag], added to gf (end.fin 1)
+  template <class TS>
+  mg_status chainT(int l, const double* c, int K, const TU* src, const TS* sdot, ChainEnd end, double alpha, TU* gf,
+                   hipStream_t st) {
     const DL& D = d[l];
-    TU* zbuf[2] = {D.za, D.zb};
-    const TU* zprev = src;
-    int cur = 0;
-    for (int k = 0; k <= K; ++k) {
-      if (slot >= nslots) return fail(MG_ERR_STATE, "reverse sweep slot overflow");
-      double* pp = dpart + h_off[slot];
-      TU* zout = (k >= 1 && k < K) ? zbuf[cur] : nullptr;
-      const TU* zin = k == 0 ? nullptr : zprev;
-      const TU* zsrc = k == 0 ? src : nullptr;
-      if (sdot_is_TH)
-        WG_SPLIT(ROWS_LAUNCH(D, k_hopT, (WGv, C, TU, TH), D.L, B(), lbs, zin, zsrc, zout,
-                             (C)c[k], D.acc, k == 0 ? 1 : 0, static_cast<const TH*>(sdot), pp));
-      else
-        WG_SPLIT(ROWS_LAUNCH(D, k_hopT, (WGv, C, TU, TU), D.L, B(), lbs, zin, zsrc, zout,
-                             (C)c[k], D.acc, k == 0 ? 1 : 0, static_cast<const TU*>(sdot), pp));
-      LAUNCH_OK();
-      ++slot;
-      if (zout) {
-        zprev = zout;
-        cur ^= 1;
+    if (slot + K + 1 > nslots) return fail(MG_ERR_STATE, "reverse sweep slot overflow");
+    Sum2* pp = dpart + h_off[slot];
+    if constexpr (std::is_same<C, float>::value) {
+      if (chain_tiled(l, K)) {
+        TileCoef cf{};
+        for (int k = 0; k <= K; ++k) cf.c[k] = (float)c[k];
+        WG_SPLIT(hipLaunchKernelGGL((k_chain_tile<WGv, TS>), dim3(chain_grid(l, K)), dim3(kTileThreads), D.tlds[K], st,
+                                    D.td, B(), K, cf, src, (const float*)D.L.invdeg, sdot, end.fin ? D.q : D.acc, end,
+                                    (float)alpha, (const float*)D.L.invdiag, gf, pp, D.tlo[K]));
+        LAUNCH_OK();
+        slot += K + 1;
+        return MG_OK;
       }
     }
+    TU* zbuf[2] = {D.za, D.zb};
+    const TU* zin = src;
+    const long ps = (long)D.rblocks;
+#define MGL_HOPT(F, H, LA, C0, CK, ZOUT)                                                                       \
+  WG_SPLIT(ROWS_LAUNCH(D, k_hopT, (WGv, F, H, LA, C, TU, TS), D.L, B(), lbs, zin, ZOUT, (C)(C0), (C)(CK), D.acc, \
+                       sdot, pp, ps, end, (C)alpha, D.q, gf))
+    TU* const none = nullptr;
+    if (K == 0) {
+      MGL_HOPT(true, false, true, c[0], 0, none);
+      LAUNCH_OK();
+    }
+    for (int k = 1; k <= K; ++k) {
+      TU* zout = k < K ? zbuf[k & 1] : nullptr;
+      if (k == 1 && K == 1) MGL_HOPT(true, true, true, c[0], c[1], none);
+      else if (k == 1) MGL_HOPT(true, true, false, c[0], c[1], zout);
+      else if (k < K) MGL_HOPT(false, true, false, 0, c[k], zout);
+      else MGL_HOPT(false, true, true, 0, c[k], none);
+      LAUNCH_OK();
+      pp += (k == 1 ? 2 : 1) * ps;
+      zin = zout;
+    }
+#undef MGL_HOPT
+    slot += K + 1;
     return MG_OK;
   }
 
   // reverse of one smoothing step whose Jacobi residual was s: g <- g - A q, gf += q
   mg_status smoothT(int l, const TH* s, TU* g, TU* gf, int& gfz, hipStream_t st) {
     const DL& D = d[l];
-    MG_TRY(chainT(l, cB(l), pl.KB, g, s, true, st));
-    hipLaunchKernelGGL((k_scale_acc<C, TU>), dim3(D.blocks), dim3(256), 0, st, D.L, B(), lbs, (const TU*)D.acc,
-                       (C)(eta(l) * theta(l)), 1, D.q, gf, gfz);
-    LAUNCH_OK();
+    MG_TRY(chainT(l, cB(l), pl.KB, (const TU*)g, s, ChainEnd{1, 1, gfz}, eta(l) * theta(l), gf, st));
     gfz = 0;
     ROWS_LAUNCH(D, k_sub_Aq, (C, TU), D.L, B(), lbs, (const TU*)g,
                        (const TU*)D.q, g);
@@ -1819,30 +1854,36 @@ struct Engine final : EngineBase {
     ROWS_LAUNCH_F(D, l == 0, k_resid, (false, C, TU, TU), D.L, B(), lbs, f, (const TU*)D.ut, uz,
                        0, D.Rv);
     LAUNCH_OK();
+    // X = P e; the iterate after the last step is not needed, so neither is its update
     const TU* ec = ck.u[l + 1];
-    ROWS_LAUNCH(D, k_prolong, (C, TU, TH), D.P, B(), lbs, ec, D.X, 0, (C)1, 0);
-    LAUNCH_OK();
-    MG_TRY(prolong(l, ec, D.ut, uz, D.x, st));
-    for (int j = 0; j < pl.nu_post; ++j) MG_TRY(smooth(l, f, D.ut, 0, D.S[pl.nu_pre + j], st));
+    if (pl.KP == 0 || pl.nu_post == 0) {
+      ROWS_LAUNCH(D, k_prolong, (C, TU, TH), D.P, B(), lbs, ec, D.X, 0, (C)1, 0);
+      LAUNCH_OK();
+    }
+    if (pl.nu_post) MG_TRY(prolong(l, ec, D.ut, uz, D.X, st));
+    for (int j = 0; j + 1 < pl.nu_post; ++j) MG_TRY(smooth(l, f, D.ut, 0, D.S[pl.nu_pre + j], st));
+    if (pl.nu_post) {
+      ROWS_LAUNCH_F(D, l == 0, k_resid, (false, C, TU, TH), D.L, B(), lbs, f, (const TU*)D.ut, 0, 1,
+                    D.S[pl.nu_pre + pl.nu_post - 1]);
+      LAUNCH_OK();
+    }
     // reverse
     MG_TRY(copy(gout, D.g, nB, st));
     int gfz = 1;
     for (int j = pl.nu_post - 1; j >= 0; --j) MG_TRY(smoothT(l, D.S[pl.nu_pre + j], D.g, gfl, gfz, st));
     // correction u += Phi_P(P ec):  dL/d ec = P^T Phi_P^T g
-    MG_TRY(chainT(l, cP(l), pl.KP, D.g, D.X, true, st));
+    MG_TRY(chainT(l, cP(l), pl.KP, (const TU*)D.g, (const TH*)D.X, ChainEnd{0, 0, 0}, 1.0, (TU*)nullptr, st));
     DL& Dn = d[l + 1];
     ROWS_LAUNCH(Dn, k_prolong, (C, TU, TU), D.PT, B(), lbs, (const TU*)D.acc,
                        Dn.gin, 0, (C)1, 0);
     LAUNCH_OK();
     MG_TRY(bwd_level(l + 1, ck.f[l + 1], nullptr, Dn.gin, Dn.gfo, nullptr, ck, st));
     // restriction rc = R Phi_R(r):  r_bar = Phi_R^T R^T rc_bar
-    ROWS_LAUNCH(D, k_prolong, (C, TU, TU), D.RT, B(), lbs, (const TU*)Dn.gfo, D.q,
+    // (to ut, free by now: the chain's last sweep writes q while others may still read its input)
+    ROWS_LAUNCH(D, k_prolong, (C, TU, TU), D.RT, B(), lbs, (const TU*)Dn.gfo, D.ut,
                        0, (C)1, 0);
     LAUNCH_OK();
-    MG_TRY(chainT(l, cR(l), pl.KR, D.q, D.Rv, false, st));
-    hipLaunchKernelGGL((k_scale_acc<C, TU>), dim3(D.blocks), dim3(256), 0, st, D.L, B(), lbs, (const TU*)D.acc, (C)1,
-                       0, D.q, gfl, gfz);
-    LAUNCH_OK();
+    MG_TRY(chainT(l, cR(l), pl.KR, (const TU*)D.ut, (const TU*)D.Rv, ChainEnd{1, 0, gfz}, 1.0, gfl, st));
     gfz = 0;
     ROWS_LAUNCH(D, k_sub_Aq, (C, TU), D.L, B(), lbs, (const TU*)D.g,
                        (const TU*)D.q, D.g);
@@ -1857,7 +1898,7 @@ struct Engine final : EngineBase {
     if (!gp) return MG_OK;
     hipLaunchKernelGGL(k_dots_final, dim3(nslots), dim3(256), 0, st, dpart, doff, dcnt, nslots, dots);
     LAUNCH_OK();
-    hipLaunchKernelGGL(k_grad_combine, dim3(1), dim3(1), 0, st, dots, ddesc, nslots, dprm, per(), pl.KB, pl.KR, gp,
+    hipLaunchKernelGGL(k_grad_combine, dim3(nblocks((long)pl.params.size())), dim3(256), 0, st, dots, ddesc, nslots, dprm, per(), pl.KB, pl.KR, gp,
                        (int)pl.params.size());
     LAUNCH_OK();
     if (pl.basis == MG_BASIS_CHEBYSHEV) {

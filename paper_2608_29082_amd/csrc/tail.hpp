@@ -772,8 +772,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<C> args, int B, 
 // per level the forward recomputation, the transposed post-smoothing and
 // prolongation (phase 0), then, after the coarser levels, the transposed
 // restriction and pre-smoothing (phase 1), in the order of operations of the
-// per-level sweeps (same bits; only the FP64 parameter dot products sum in
-// another order).  What bounds it is what bounds k_tail: ~45 dependent sweeps a
+// per-level sweeps (same bits).  What bounds it is what bounds k_tail: ~45 dependent sweeps a
 // level, where the per-level form paid ~75 launches.  A transposed hop
 // z = G^T y is the neighbour sum of the row-scaled vector, so it reads LDS like a
 // forward hop.  What a level keeps between its phases (S_j, the residual, P e, g
@@ -792,11 +791,11 @@ struct TailBwdArgs {
   TailArgs<C> T;            // off_u / off_f: gradients of a level's output and right-hand side
   TailBwdLevel<C> b[kTailMaxLevels];
   int off_dot;              // byte offset in LDS: dot products of a visit per wavefront
-  double* part;             // slot s of column c at s B + c
+  Sum2* part;               // slot s of column c at s B + c
 };
 
 template <int RPT, int W, bool WAVE, bool SAME, bool VC, bool GC, bool WG, class C>
-__device__ __forceinline__ void tail_bwd_visit(const TailBwdArgs<C>& A, C* sm, uint32_t wk, double* dot, const C* prm,
+__device__ __forceinline__ void tail_bwd_visit(const TailBwdArgs<C>& A, C* sm, uint32_t wk, Sum2* dot, const C* prm,
                                                int q, int phase, int B, const C* uin, const C* gout, C* gfo, C* gul) {
   using Rows = TailRows<RPT, W, WAVE, SAME, VC, GC, WG, C>;
   const TailArgs<C>& T = A.T;
@@ -825,10 +824,10 @@ __device__ __forceinline__ void tail_bwd_visit(const TailBwdArgs<C>& A, C* sm, u
       for (int r = 0; r < RPT; ++r) z[r] = d[M.ic[r]];
   };
   auto dots = [&](const C (&z)[RPT]) __attribute__((always_inline)) {
-    double d = 0.0;
+    Sum2 d{0.0, 0.0};
     if (M.act) {
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) d += M.ok[r] ? (double)z[r] * (double)s[r] : 0.0;
+      for (int r = 0; r < RPT; ++r) d = sum2_add(d, M.ok[r] ? (double)z[r] * (double)s[r] : 0.0);
       d = wave_sum(d);
     }
     if (lane == 0) dot[nd * 16 + wave] = d;
@@ -1006,15 +1005,15 @@ __device__ __forceinline__ void tail_bwd_visit(const TailBwdArgs<C>& A, C* sm, u
   tail_sync<WAVE>();
   // the visit's dot products over the wavefronts, in order
   for (int t = threadIdx.x; t < nd; t += Rows::nt) {
-    double d = 0.0;
-    for (int w = 0; w < Rows::nt / 64; ++w) d += dot[t * 16 + w];
+    Sum2 d{0.0, 0.0};
+    for (int w = 0; w < Rows::nt / 64; ++w) d = sum2_add(d, dot[t * 16 + w]);
     A.part[(size_t)((phase ? tb.slot1 : tb.slot0) + t) * B + col] = d;
   }
   tail_sync<WAVE>();
 }
 
 template <bool WG, class C>
-__device__ __forceinline__ void tail_bwd_level(const TailBwdArgs<C>& A, C* sm, C* wk, double* dot, const C* prm, int q,
+__device__ __forceinline__ void tail_bwd_level(const TailBwdArgs<C>& A, C* sm, C* wk, Sum2* dot, const C* prm, int q,
                                                int phase, int B, const C* uin, const C* gout, C* gfo, C* gul) {
   const int rpt = A.T.lv[q].rpt, w = A.T.lv[q].w;
   const uint32_t wa = lds_addr(wk);
@@ -1058,7 +1057,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_bwd(TailBwdArgs<C> args, 
   C* wk = reinterpret_cast<C*>(tail_smem + T.off_wk);
   C* prm = reinterpret_cast<C*>(tail_smem + T.off_prm);
   double* inv = reinterpret_cast<double*>(tail_smem + T.off_inv);
-  double* dot = reinterpret_cast<double*>(tail_smem + A.off_dot);
+  Sum2* dot = reinterpret_cast<Sum2*>(tail_smem + A.off_dot);
   tail_params(T, prm, inv);
   __syncthreads();
   const int last = T.nl - 1;
