@@ -170,7 +170,9 @@ mg_status mg_workspace_bytes(const mg_hierarchy* h, const mg_params* p, const mg
  * of 16 also tile the levels of >= 2048 rows for the fused K-hop
  * convolution (unless MG_FLAG_NO_TILES); the tile lists (about 50 bytes per
  * unknown of those levels at K = 3) are allocated by the library outside
- * the workspace and freed by mg_destroy.  Synchronises `stream` before
+ * the workspace and freed by mg_destroy.  FP64 contexts, and FP32 contexts of
+ * other widths, do so for levels of up to about a million entries (rows x
+ * nrhs), with lists of about 40 bytes per unknown.  Synchronises `stream` before
  * returning. */
 mg_status mg_setup(const mg_hierarchy* h, const mg_params* p, const mg_options* o,
                    void* workspace, size_t workspace_bytes, void* stream, mg_ctx** out);

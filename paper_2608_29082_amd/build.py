@@ -11,6 +11,7 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -20,7 +21,7 @@ LIB = os.path.join(HERE, "libmgl.so")
 ARCH = os.environ.get("MGL_OFFLOAD_ARCH", "gfx950")
 
 HIP_FLAGS = [
-    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
+    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-result", "-Wno-unused-function",
 ]
@@ -33,18 +34,36 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
+SOURCES = ("mgl.hip", "tail_f32.hip", "tail_f64.hip", "helm.hip", "hierarchy.cpp")
+
+
 def build(verbose: bool = True) -> str:
-    """Compile csrc/mgl.hip, csrc/helm.hip and csrc/hierarchy.cpp into libmgl.so (always recompiles)."""
-    srcs = [os.path.join(CSRC, "mgl.hip"), os.path.join(CSRC, "helm.hip"), os.path.join(CSRC, "hierarchy.cpp")]
+    """Compile the sources of csrc/ side by side and link libmgl.so (always recompiles)."""
     tmp = LIB + ".tmp"
-    cmd = [hipcc(), *HIP_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", *srcs, "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    # the host pass does not know the packed-fp32 feature; that warning is harmless
-    msgs = [ln for ln in (res.stdout + res.stderr).splitlines() if "packed-fp32-ops" not in ln]
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
+    objs = [f"{tmp}.{s.rsplit('.', 1)[0]}.o" for s in SOURCES]
+    msgs = []
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        # the host pass does not know the packed-fp32 feature; that warning is harmless
+        out = [ln for ln in (res.stdout + res.stderr).splitlines() if "packed-fp32-ops" not in ln]
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + "\n".join(out))
+        msgs.extend(out)
+
+    def compile_one(k):
+        run([hipcc(), *HIP_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", "-c", os.path.join(CSRC, SOURCES[k]), "-o", objs[k]])
+
+    try:
+        with ThreadPoolExecutor(len(SOURCES)) as pool:
+            list(pool.map(compile_one, range(len(SOURCES))))
+        run([hipcc(), f"--offload-arch={ARCH}", "-shared", *objs, "-o", tmp])
+    finally:
+        for o in objs:
+            if os.path.exists(o):
+                os.remove(o)
     if verbose and msgs:
         print("\n".join(msgs), file=sys.stderr)
     os.replace(tmp, LIB)

@@ -743,6 +743,214 @@ __global__ __launch_bounds__(kTileThreads) void k_conv_tile(TileDev T, int B, in
   }
 }
 
+// ---------------------------------------------------------------- narrow batches: patches
+// A step of the cycle on a level above the coarse tail - its input, all K Horner hops of its
+// convolution and the update of its result - as one launch for batches that are no multiple of
+// kTileCols columns, and for FP64.  One workgroup computes the own nodes of a patch (tiles.hpp, as for
+// k_conv_tile) and NC columns, one listed node a work-item: its graph columns and its input stay in
+// registers, the hops are exchanged through LDS.  The input on the patch's K-hop neighbourhood comes from
+//   FRONT 0: x [xsc]                   (xsc: Jacobi scale of a zero iterate's residual)
+//   FRONT 1: (x - A u) [xsc]           residual of the iterate u
+//   FRONT 2: P x                       prolongation
+// so a smoothing step is one launch instead of K + 1, reading u and writing out (other memory: the
+// neighbouring patches still read u).  What bounds it is latency, of the launch and of the four dependent
+// loads (list bounds, node, row, neighbours): 5.7 us a step of three hops, the mean over 255 x 255 x 1 and
+// 127 x 127 x 1, where the four sweeps it replaces took 11.
+// Arithmetic per node and column as in k_resid, k_prolong and k_hop (same order of the sums).
+constexpr int kPatchThreads = 512;   // at most, and the listed nodes at distance <= K - 1 with them
+struct PatchDev {
+  int ntiles, KM, wg;
+  const int *toff, *node, *cnt, *goff;   // as TileDev
+  const uint16_t* lcol;                  // local graph columns + 1 (0: padding, the row of zeros)
+};
+template <class C> struct PatchCoef {
+  C c[kTileMaxK + 1];
+};
+template <class C, int NC> struct alignas(NC * sizeof(C) < 16 ? NC * sizeof(C) : 16) PatchRow {
+  C v[NC];
+};
+
+// WIDTH: slots a row whose columns are held (8), or 0: read at each hop.
+//   out = Phi(input)                        (mode 0)
+//   out = (uin ? uin : 0) + scale Phi       (mode 1; uin may be out)
+template <int FRONT, int WIDTH, int NC, bool WG, class C>
+__global__ __launch_bounds__(kPatchThreads) void k_patch(PatchDev T, Lvl<C> L, Xfer<C> P, int B, int K,
+                                                         PatchCoef<C> cf, const C* __restrict__ x,
+                                                         const C* __restrict__ u, const C* __restrict__ xsc,
+                                                         const C* uin, C* out, int mode, C scale, int y0, int y1) {
+  using Row = PatchRow<C, NC>;
+  extern __shared__ __align__(16) char patch_smem[];
+  Row* S = reinterpret_cast<Row*>(patch_smem);   // each of the three buffers after a row of zeros
+  const int nch = (B + NC - 1) / NC;
+  const long W = (long)T.ntiles * nch;
+  const int xc = blockIdx.x & 7;                 // an XCD's patches are neighbours, as in k_conv_tile
+  const long it = W * xc / 8 + (blockIdx.x >> 3);
+  if (it >= W * (xc + 1) / 8) return;
+  const int t = (int)(it / nch), c0 = (int)(it - (long)t * nch) * NC;
+  const int nt = blockDim.x, r = threadIdx.x;
+  const int* cn = T.cnt + (size_t)t * (T.KM + 1);
+  const int cK = ld_const(cn + K), m = ld_const(cn + K - 1), own = ld_const(cn);
+  const int base = ld_const(T.toff + t), m0 = ld_const(T.goff + t);
+  int nd[2], cb[NC];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) nd[e] = T.node[base + min(r + e * nt, cK - 1)];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) cb[c] = min(c0 + c, B - 1);
+  // this work-item's row of the graph
+  const uint16_t* lcp = T.lcol + m0 + (size_t)min(r, m - 1) * T.wg;
+  ushort4 lc[WIDTH ? WIDTH / 4 : 1];
+  C ew[WG && WIDTH ? WIDTH : 1];
+  if constexpr (WIDTH != 0) {
+#pragma unroll
+    for (int k = 0; k < WIDTH / 4; ++k) {
+      if (4 * k >= T.wg) break;
+      lc[k] = reinterpret_cast<const ushort4*>(lcp)[k];
+      if constexpr (WG) {
+#pragma unroll
+        for (int q = 4 * k; q < 4 * k + 4; ++q) ew[q] = L.gval[(size_t)q * L.ld + nd[0]];
+      }
+    }
+  }
+  const C idg = L.invdeg[nd[0]];
+  C ov[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) ov[c] = (uin && r < own) ? uin[(size_t)nd[0] * B + cb[c]] : C(0);
+  // the input on the listed nodes
+  C xv[2][NC];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    if constexpr (FRONT == 2) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) xv[e][c] = C(0);
+      for (int k = 0; k < P.w; k += 2) {
+        int j[2];
+        C w[2], v[2][NC];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const size_t o = (size_t)(k + q) * P.n + nd[e];
+          j[q] = P.col[o];
+          w[q] = P.val[o];
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) v[q][c] = x[(size_t)j[q] * B + cb[c]];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) xv[e][c] += w[q] * v[q][c];
+      }
+    } else {
+      const C di = xsc ? xsc[nd[e]] : C(1);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) xv[e][c] = x[(size_t)nd[e] * B + cb[c]];
+      if constexpr (FRONT == 1) {
+        C uv[NC], s[NC];
+        const C dg = L.diag[nd[e]];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          uv[c] = u[(size_t)nd[e] * B + cb[c]];
+          s[c] = C(0);
+        }
+        for (int k = 0; k < L.w; k += 4) {
+          int j[4];
+          C v[4], un[4][NC];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const size_t o = (size_t)(k + q) * L.ld + nd[e];
+            j[q] = L.col[o];
+            v[q] = L.val[o];
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) un[q][c] = u[(size_t)j[q] * B + cb[c]];
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) s[c] += v[q] * un[q][c];
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) xv[e][c] = xv[e][c] - (s[c] + dg * uv[c]);
+      }
+      if (xsc) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) xv[e][c] *= di;
+      }
+    }
+  }
+  if (r < 3) {
+    Row z;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) z.v[c] = C(0);
+    S[r == 0 ? 0 : (r == 1 ? y0 : y1)] = z;
+  }
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+    if (r + e * nt < cK) {
+      Row z;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) z.v[c] = xv[e][c];
+      S[1 + r + e * nt] = z;
+    }
+  __syncthreads();
+  int yi = 0;                                    // the hop's input buffer
+  for (int hp = 1; hp <= K; ++hp) {
+    const int rows = hp == K ? own : ld_const(cn + K - hp);
+    const int yo = (hp & 1) ? y0 : y1;
+    if (r < rows) {
+#pragma clang fp contract(off)
+      C s[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) s[c] = C(0);
+      auto add4 = [&](ushort4 jj, const C* w) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+        const int j[4] = {jj.x, jj.y, jj.z, jj.w};
+        Row z[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) z[q] = S[yi + j[q]];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            C v = z[q].v[c];
+            if constexpr (WG) v *= w[q];
+            s[c] += v;
+          }
+      };
+      if constexpr (WIDTH != 0) {
+#pragma unroll
+        for (int k = 0; k < WIDTH / 4; ++k) {
+          if (4 * k >= T.wg) break;
+          add4(lc[k], WG ? &ew[4 * k] : nullptr);
+        }
+      } else {
+        for (int k = 0; k < T.wg; k += 4) {
+          C w[4];
+          if constexpr (WG) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w[q] = L.gval[(size_t)(k + q) * L.ld + nd[0]];
+          }
+          add4(reinterpret_cast<const ushort4*>(lcp)[k / 4], w);
+        }
+      }
+      const C cc = cf.c[K - hp];
+      Row z;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) z.v[c] = hop_value(hp == 1 ? cf.c[K] : C(1), idg, s[c], cc, xv[0][c]);
+      if (hp < K) {
+        S[yo + 1 + r] = z;
+      } else {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          if (c0 + c < B) out[(size_t)nd[0] * B + c0 + c] = mode == 0 ? z.v[c] : hop_update(ov[c], scale, z.v[c]);
+      }
+    }
+    if (hp < K) __syncthreads();
+    yi = yo;
+  }
+}
+
 // out = (oz ? 0 : out) + alpha * x
 template <class C, class TX, class TO>
 __global__ __launch_bounds__(256) void k_axpy(int n, int B, int lbs, const TX* __restrict__ x, C alpha,
@@ -901,7 +1109,7 @@ __global__ __launch_bounds__(256) void k_coarse(int n, int B, const double* __re
 // W[0:n, 0:n] of the row-major n x 2n array W (W[:, n:2n] must be I on
 // entry).  One block of 1024 threads.  On exit W[:, n:2n] = A^{-1}.
 // *info = 0 on success, k+1 if the pivot of column k is zero.
-__global__ __launch_bounds__(1024) void k_gauss_jordan(int n, double* W, int* info) {
+static __global__ __launch_bounds__(1024) void k_gauss_jordan(int n, double* W, int* info) {
   __shared__ double sval[1024];
   __shared__ int sidx[1024];
   __shared__ int piv_s;
@@ -1047,8 +1255,8 @@ __global__ __launch_bounds__(256) void k_outer_resid(Lvl<double> L, int B, int l
 
 // norms[b] = sqrt(sum over blocks of part[block][b]); one block per column,
 // fixed strided order and fixed tree (deterministic).
-__global__ __launch_bounds__(256) void k_norm_final(const double* __restrict__ part, int nblk, int B,
-                                                    double* __restrict__ norms, const int* __restrict__ act) {
+static __global__ __launch_bounds__(256) void k_norm_final(const double* __restrict__ part, int nblk, int B,
+                                                           double* __restrict__ norms, const int* __restrict__ act) {
   __shared__ double red[256];
   const int b = blockIdx.x;
   if (act && act[b] == 0) return;   // a stopped column keeps its last norm
@@ -1105,10 +1313,10 @@ __global__ __launch_bounds__(256) void k_colsq(int n, int B, int lbs, int chunk,
 //   kind 1: L = sum_b rn_b,  alpha_b = g / rn_b (0 when rn_b = 0),  beta_b = 0
 // so that dL/du_b = -alpha_b A^T r_b and dL/df_b = alpha_b r_b - beta_b f_b,
 // scaled by the incoming cotangent g = *gseed (1 when gseed is null).
-__global__ __launch_bounds__(256) void k_loss_coef(const double* __restrict__ rn, const double* __restrict__ fn,
-                                                   int B, int kind, const double* __restrict__ gseed,
-                                                   double* __restrict__ alpha, double* __restrict__ beta,
-                                                   double* __restrict__ loss) {
+static __global__ __launch_bounds__(256) void k_loss_coef(const double* __restrict__ rn, const double* __restrict__ fn,
+                                                          int B, int kind, const double* __restrict__ gseed,
+                                                          double* __restrict__ alpha, double* __restrict__ beta,
+                                                          double* __restrict__ loss) {
   __shared__ double red[256];
   const int b = threadIdx.x;
   const double g = gseed ? gseed[0] : 1.0;
@@ -1169,8 +1377,8 @@ __global__ __launch_bounds__(256) void k_loss_grad(Lvl<double> L, int B, int lbs
 
 // Per-column solver bookkeeping after the residual of iterate m.
 // st: [0,B) active, [B,2B) iters, [2B,3B) status; 3B: active count.
-__global__ void k_solve_check(const double* __restrict__ norms, double* __restrict__ fnorm,
-                              double* __restrict__ init, int* st, int B, double rtol, double divf, int first) {
+static __global__ void k_solve_check(const double* __restrict__ norms, double* __restrict__ fnorm,
+                                     double* __restrict__ init, int* st, int B, double rtol, double divf, int first) {
   __shared__ int cnt[256];
   const int b = threadIdx.x;
   int act = 0;
@@ -1246,8 +1454,8 @@ __global__ __launch_bounds__(256) void k_put_column(int w, int ld, int n, int nv
 
 // u[i][b] = w[i][b] for the columns whose update count iters[b] is odd (the
 // solver alternates the iterate between u and w, one buffer per update)
-__global__ __launch_bounds__(256) void k_copy_odd(int n, int B, int lbs, const int* __restrict__ iters,
-                                                  const double* __restrict__ w, double* __restrict__ u) {
+static __global__ __launch_bounds__(256) void k_copy_odd(int n, int B, int lbs, const int* __restrict__ iters,
+                                                         const double* __restrict__ w, double* __restrict__ u) {
   MGL_ROW_LANE(n)
   for (int b = lane; b < B; b += (1 << lbs))
     if (iters[b] & 1) u[(size_t)i * B + b] = w[(size_t)i * B + b];
@@ -1554,9 +1762,9 @@ __global__ __launch_bounds__(256) void k_sub_Aq(Lvl<C> L, int B, int lbs, const 
 }
 
 // dots[s] = sum_{g < cnt[s]} part[off[s] + g], rounded here
-__global__ __launch_bounds__(256) void k_dots_final(const Sum2* __restrict__ part, const long* __restrict__ off,
-                                                    const int* __restrict__ cnt, int nslots,
-                                                    double* __restrict__ dots) {
+static __global__ __launch_bounds__(256) void k_dots_final(const Sum2* __restrict__ part, const long* __restrict__ off,
+                                                           const int* __restrict__ cnt, int nslots,
+                                                           double* __restrict__ dots) {
   __shared__ Sum2 red[4];
   const int s = blockIdx.x;
   if (s >= nslots) return;
@@ -1577,9 +1785,9 @@ __global__ __launch_bounds__(256) void k_dots_final(const Sum2* __restrict__ par
 // Smoother dot e = <(M^T)^k g, s> with s = D^{-1}(f - A u):
 //   dc_k += eta theta e,  deta += theta c_k e,  dtheta += eta c_k e.
 // Transfer dots give dc_k directly.
-__global__ __launch_bounds__(256) void k_grad_combine(const double* __restrict__ dots, const int* __restrict__ desc,
-                                                      int nslots, const double* __restrict__ prm, int per, int KB,
-                                                      int KR, double* __restrict__ g, int np) {
+static __global__ __launch_bounds__(256) void k_grad_combine(const double* __restrict__ dots, const int* __restrict__ desc,
+                                                             int nslots, const double* __restrict__ prm, int per, int KB,
+                                                             int KR, double* __restrict__ g, int np) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= np) return;
   const int l = t / per, o = t - l * per;
@@ -1604,7 +1812,7 @@ __global__ __launch_bounds__(256) void k_grad_combine(const double* __restrict__
 // the power-series coefficients the cycle ran with:
 //   a_m = sum_k c_k (-1)^k T_k[m]   =>   dL/dc_k = (-1)^k sum_m T_k[m] dL/da_m
 // for every convolution of every level (one work-item per level).
-__global__ void k_cheb_grad(double* __restrict__ g, int L, int per, int KB, int KR, int KP, ChebTab T) {
+static __global__ void k_cheb_grad(double* __restrict__ g, int L, int per, int KB, int KR, int KP, ChebTab T) {
   const int l = blockIdx.x * blockDim.x + threadIdx.x;
   if (l >= L) return;
   double* gl = g + (size_t)l * per + 2;

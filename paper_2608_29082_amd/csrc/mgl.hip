@@ -28,6 +28,10 @@
 #include "tail.hpp"
 #include "tiles.hpp"
 
+namespace mgl {
+MGL_TAIL_KERNELS(extern, float)
+MGL_TAIL_KERNELS(extern, double)
+}  // namespace mgl
 using namespace mgl;
 
 namespace {
@@ -219,6 +223,8 @@ struct Engine final : EngineBase {
     size_t tlds[kTileMaxK + 1] = {};  // and its size in bytes
     unsigned tgrid[kTileMaxK + 1] = {};  // persistent grid (a multiple of 8 blocks)
     int tocc[kTileMaxK + 1] = {};        // resident workgroups per compute unit
+    PatchDev pd{};                  // patches of narrow batches (pd.ntiles == 0: none)
+    int pmax[kTileMaxK + 1] = {};   // most nodes at distance <= k in a patch
   };
   std::vector<DL> d;
   Lvl<double> L64{};                // level-0 operator in FP64 (outer residual)
@@ -242,6 +248,7 @@ struct Engine final : EngineBase {
   size_t kr_own_bytes = 0;
   char* tile_mem = nullptr;         // tile lists of the fused convolution, allocated by the library
   size_t tile_mem_bytes = 0;
+  char* patch_mem = nullptr;        // patch lists, allocated by the library
   // coarse tail (levels tail_lt .. J-1 in LDS, one workgroup per column)
   int tail_lt = -1;                 // shallowest level whose tail fits in LDS
   int tail_own = -1;                // first of its levels that have no fused-convolution tiles
@@ -273,6 +280,7 @@ struct Engine final : EngineBase {
     if (owns_ws && wsbase) (void)hipFree(wsbase);
     if (kr_own) (void)hipFree(kr_own);
     if (tile_mem) (void)hipFree(tile_mem);
+    if (patch_mem) (void)hipFree(patch_mem);
     if (hcount) (void)hipHostFree(hcount);
     if (hmap) (void)hipHostFree(hmap);
     if (colhost) (void)hipHostFree(colhost);
@@ -602,8 +610,10 @@ struct Engine final : EngineBase {
     if (info != 0) return fail(MG_ERR_SHAPE, "coarsest matrix is singular (zero pivot in column " + std::to_string(info - 1) + ")");
     MG_TRY(setup_tiles(st));
     MG_TRY(setup_tail());
+    if (!bwd()) MG_TRY(setup_patches(st));
     if (bwd()) {
       MG_TRY(setup_bwd_tail());
+      MG_TRY(setup_patches(st));
       h_off.clear(); h_cnt.clear(); h_desc.clear();
       enum_slots(0, false);
       HIP_TRY(hipMemcpyAsync(doff, h_off.data(), h_off.size() * sizeof(long), hipMemcpyHostToDevice, st));
@@ -950,6 +960,115 @@ struct Engine final : EngineBase {
     return MG_OK;
   }
 
+  // Patches of the levels above the coarse tail that have no tiles (k_patch): for FP64 cycles and for
+  // FP32 with widths that are no multiple of kTileCols, up to patch_limit entries.  Not with BF16 intermediates, which the
+  // per-hop sweeps round.  The patch lists take about 30 bytes a node.
+  mg_status setup_patches(hipStream_t st) {
+    if (!std::is_same<TH, TU>::value || (pl.flags & MG_FLAG_NO_TILES)) return MG_OK;
+    int KM = 0;
+    for (int K : {pl.KB, pl.KR, pl.KP})
+      if (K >= 2) KM = std::max(KM, K);
+    if (KM < 2 || KM > kTileMaxK) return MG_OK;
+    const int J = pl.J;
+    int lt = tail_lt >= 0 ? tail_lt : J - 1;
+    if (bwd()) lt = std::max(lt, btail_lt >= 0 ? btail_lt : J - 1);
+    std::vector<TilePlan> tp(J);
+    size_t bytes = 0;
+    auto a256 = [](size_t b) { return (std::max<size_t>(b, 1) + 255) & ~size_t(255); };
+    for (int l = 0; l < std::min(lt, J - 1); ++l) {
+      const HLevel& H = pl.lv[l];
+      if (H.n < kTileMinRows || d[l].td.ntiles || (long)H.n * pl.B > patch_limit(KM)) continue;
+      const HEll& g = H.graph_is_A ? H.off : H.graph;
+      // 12 x 12 nodes: a cycle on 257^2 x 1 takes 6.7 / 7.0 / 7.0 ms a solve with sides of 12 / 8 / 16,
+      // one on 385^2 x 7 FP64 590 / 704 / 607 us
+      for (int side : {12, 8, 6, 4}) {
+        if (build_tiles(H.n, g.ld, g.w, g.col.data(), KM, side, side, tp[l], MGL_TILE_GROUP) &&
+            tp[l].maxcnt[KM - 1] <= kPatchThreads && tp[l].maxcnt[KM] <= 2 * kPatchThreads &&
+            patch_lds(tp[l].maxcnt.data(), KM, 4) <= 65536)
+          break;
+        tp[l] = TilePlan{};
+      }
+      const TilePlan& t = tp[l];
+      if (!t.ntiles) continue;
+      if (!check_tiles(H.n, g.ld, g.col.data(), t))
+        return fail(MG_ERR_STATE, "patch lists of level " + std::to_string(l) + " are inconsistent");
+      bytes += a256((t.ntiles + 1) * sizeof(int)) * 2 + a256(t.node.size() * sizeof(int)) +
+               a256(t.cnt.size() * sizeof(int)) + a256(t.lcol.size() * sizeof(uint16_t));
+    }
+    if (!bytes) return MG_OK;
+    HIP_TRY(hipMalloc(&patch_mem, bytes));
+    char* p = patch_mem;
+    bool ok = true;
+    auto put = [&](const void* src, size_t b) -> const void* {
+      void* dst = p;
+      p += a256(b);
+      if (b && hipMemcpyAsync(dst, src, b, hipMemcpyHostToDevice, st) != hipSuccess) ok = false;
+      return dst;
+    };
+    for (int l = 0; l < J; ++l) {
+      const TilePlan& t = tp[l];
+      if (!t.ntiles) continue;
+      PatchDev& v = d[l].pd;
+      v.ntiles = t.ntiles; v.KM = t.KM; v.wg = t.wg;
+      v.toff = static_cast<const int*>(put(t.toff.data(), t.toff.size() * sizeof(int)));
+      v.goff = static_cast<const int*>(put(t.goff.data(), t.goff.size() * sizeof(int)));
+      v.node = static_cast<const int*>(put(t.node.data(), t.node.size() * sizeof(int)));
+      v.cnt = static_cast<const int*>(put(t.cnt.data(), t.cnt.size() * sizeof(int)));
+      v.lcol = static_cast<const uint16_t*>(put(t.lcol.data(), t.lcol.size() * sizeof(uint16_t)));
+      std::copy(t.maxcnt.begin(), t.maxcnt.end(), d[l].pmax);
+    }
+    HIP_TRY(hipStreamSynchronize(st));   // the host lists are freed on return
+    if (!ok) return fail(MG_ERR_HIP, "patch list upload failed");
+    return MG_OK;
+  }
+  // LDS of one patch and NC columns: input, hop buffers at distance <= K - 1 and <= K - 2, three rows of zeros
+  static size_t patch_lds(const int* most, int K, int NC) {
+    return (size_t)(most[K] + most[K - 1] + (K >= 3 ? most[K - 2] : 0) + 3) * NC * sizeof(C);
+  }
+  // Most entries (rows x columns) of a level whose convolutions of order K run over patches.  A patch
+  // saves launches and round trips, but reads its lists and the operator again for every four columns and
+  // computes its halo twice over, so it loses where the sweeps fill the chip.  Cycle times with the level
+  // by sweeps -> by patches, K = 3: 513^2 x 4 FP32 at 260 K entries 309 -> 295 us, 257^2 x 40 FP32 at
+  // 645 K 412 -> 452, 1025^2 at 1.05 M 375 -> 502; K = 2: 513^2 x 3 at 195 K 293 -> 282, 257^2 x 16 FP64 at
+  // 258 K 378 -> 394.  With edge weights, which a patch reads once instead of at every hop, from K = 3 on:
+  // 513^2 x 5 FP64 at 1.3 M 744 -> 575, 257^2 x 32 FP64 (K = 4) at 2.1 M 876 -> 982.
+  long patch_limit(int K) const { return K < 3 ? 1L << 17 : (wgt() ? 3L << 19 : 1L << 18); }
+  bool patched(int l, int K) const {
+    return d[l].pd.ntiles > 0 && K >= 2 && K <= d[l].pd.KM && (long)d[l].L.n * B() <= patch_limit(K);
+  }
+
+  // one launch over patches (k_patch): out = Phi(input) or (uin ? uin : 0) + scale Phi(input)
+  template <int FRONT>
+  mg_status patch(int l, const double* c, int K, const TU* x, const TU* u, const C* xsc, const TU* uin, TU* out,
+                  int mode, double scale, hipStream_t st) {
+    if constexpr (std::is_same<TH, TU>::value) {
+      const DL& D = d[l];
+      PatchCoef<C> cf{};
+      for (int k = 0; k <= K; ++k) cf.c[k] = (C)c[k];
+      const int* mx = D.pmax;
+      const int nt = (std::max(mx[K - 1], (mx[K] + 1) / 2) + 63) / 64 * 64;
+      const int y0 = mx[K] + 1, y1 = y0 + mx[K - 1] + 1;
+      auto go = [&](auto nc) -> mg_status {
+        constexpr int NC = decltype(nc)::value;
+        const long W = (long)D.pd.ntiles * ((B() + NC - 1) / NC);
+        const unsigned grid = (unsigned)(8 * ((W + 7) / 8));
+        const size_t lds = patch_lds(mx, K, NC);
+        const double bytes = nB(l) * sizeof(C) * (FRONT == 1 ? 2 : 1) + nB(l) * sizeof(C) * (mode && uin ? 2 : 1) +
+                             (FRONT == 1 ? bytes_A(l) : (FRONT == 2 ? bytes_X(D.P) : 0.0)) +
+                             (double)D.L.wg * D.L.n * (4 + (wgt() ? sizeof(C) : 0)) + (double)D.L.n * sizeof(C);
+#define MGL_PATCH(W_)                                                                                               TIMED(MG_KF_CONV, bytes,                                                                                                WG_SPLIT(hipLaunchKernelGGL((k_patch<FRONT, W_, NC, WGv, C>), dim3(grid), dim3(nt), lds, st, D.pd, D.L, D.P,                                     B(), K, cf, x, u, xsc, uin, out, mode, (C)scale, y0, y1)))
+        if (D.pd.wg <= 8) MGL_PATCH(8);
+        else MGL_PATCH(0);
+#undef MGL_PATCH
+        return MG_OK;
+      };
+      if (B() == 1) return go(std::integral_constant<int, 1>{});
+      return go(std::integral_constant<int, 4>{});
+    } else {
+      return fail(MG_ERR_STATE, "patches need cycles of one type");
+    }
+  }
+
   bool tiled(int l, int K, const void* x, const void* out) const {
     const TileDev& td = d[l].td;
     return td.ntiles > 0 && K >= 2 && K <= td.KM && x != out && ((uintptr_t)x % 16) == 0 &&
@@ -1109,6 +1228,10 @@ struct Engine final : EngineBase {
       return MG_OK;
     }
     if (tiled(l, K, x, u)) return conv_tile<TH, TU>(l, c, K, x, u, 1, scale, oz, st);
+    if constexpr (std::is_same<TH, TU>::value) {
+      if (patched(l, K) && (const void*)x != u)
+        return patch<0>(l, c, K, x, nullptr, nullptr, oz ? nullptr : u, u, 1, scale, st);
+    }
     const TH* yin = x;
     double a = c[K];
     TH* buf[2] = {D.ya, D.yb};
@@ -1131,12 +1254,22 @@ struct Engine final : EngineBase {
       if (uz && !keep_s && pl.KB >= 2 && !pl.nv && tiled(l, pl.KB, f, u))
         return conv_tile<TU, TU>(l, cB(l), pl.KB, f, u, 1, eta(l) * theta(l), 1, st, D.L.invdiag);
     }
+    if (uz && !keep_s && !pl.nv && patched(l, pl.KB) && f != u)
+      return patch<0>(l, cB(l), pl.KB, f, nullptr, D.L.invdiag, nullptr, u, 1, eta(l) * theta(l), st);
     TIMED(MG_KF_RESID, nB(l) * (sizeof(TU) * (uz ? 1 : 2) + sizeof(TH)) + (uz ? 0.0 : bytes_A(l)) +
                            (double)D.L.n * sizeof(C),
           PCV_SPLIT(ROWS_LAUNCH_F(D, l == 0, k_resid, (PCVv, C, TU, TH), D.L, B(), lbs, f, u, uz, 1, s)));
     return conv_add(l, cB(l), pl.KB, s, eta(l) * theta(l), u, uz, st);
   }
 
+  // rc = R_l y
+  mg_status restrict_plain(int l, const TH* y, TU* rc, hipStream_t st) {
+    const DL& D = d[l];
+    TIMED(MG_KF_RESTRICT, nB(l) * sizeof(TH) + bytes_X(D.R) + nB(l + 1) * sizeof(TU),
+          RESTRICT_LAUNCH(d[l + 1].blocks, (false, C, TU, TH, TU), D.R, D.L, B(), lbs, 0, y, (C)0,
+                          (const TU*)nullptr, (C)0, (const TU*)nullptr, (const TU*)nullptr, 0, (C)1, rc));
+    return MG_OK;
+  }
   // rc = R_l Phi_R(f - A u)
   mg_status restrict_(int l, const TU* f, const TU* u, int uz, TU* rc, hipStream_t st) {
     const DL& D = d[l];
@@ -1149,6 +1282,14 @@ struct Engine final : EngineBase {
             RESTRICT_LAUNCH(cb, (false, C, TU, TU, TU), D.R, D.L, B(), lbs, 2,
                                (const TU*)nullptr, (C)0, (const TU*)nullptr, (C)0, f, u, uz, (C)c[0], rc));
       return MG_OK;
+    }
+    if constexpr (std::is_same<TH, TU>::value) {
+      if (patched(l, K) && (uz || !pl.nv)) {
+        // y = Phi_R(r), the residual on the way in, then the plain restriction of y
+        if (uz) MG_TRY((patch<0>(l, c, K, f, nullptr, nullptr, nullptr, D.ya, 0, 1.0, st)));
+        else MG_TRY((patch<1>(l, c, K, f, u, nullptr, nullptr, D.ya, 0, 1.0, st)));
+        return restrict_plain(l, D.ya, rc, st);
+      }
     }
     TIMED(MG_KF_RESID, nB(l) * sizeof(TU) * (uz ? 2 : 3) + (uz ? 0.0 : bytes_A(l)),
           PCV_SPLIT(ROWS_LAUNCH_F(D, l == 0, k_resid, (PCVv, C, TU, TU), D.L, B(), lbs, f, u, uz, 0,
@@ -1165,10 +1306,13 @@ struct Engine final : EngineBase {
     if (tiled(l, K, D.r, D.ya)) {
       // y = Phi_R(r) in one fused launch, then the plain restriction of y
       MG_TRY(conv_tile<TU, TH>(l, c, K, D.r, D.ya, 0, 1.0, 0, st));
-      TIMED(MG_KF_RESTRICT, nB(l) * sizeof(TH) + bytes_X(D.R) + nB(l + 1) * sizeof(TU),
-            RESTRICT_LAUNCH(cb, (false, C, TU, TH, TU), D.R, D.L, B(), lbs, 0, (const TH*)D.ya, (C)0,
-                            (const TU*)nullptr, (C)0, (const TU*)nullptr, (const TU*)nullptr, 0, (C)1, rc));
-      return MG_OK;
+      return restrict_plain(l, D.ya, rc, st);
+    }
+    if constexpr (std::is_same<TH, TU>::value) {
+      if (patched(l, K)) {
+        MG_TRY((patch<0>(l, c, K, D.r, nullptr, nullptr, nullptr, D.ya, 0, 1.0, st)));
+        return restrict_plain(l, D.ya, rc, st);
+      }
     }
     MG_TRY(hop<TU, TU, TH>(l, D.r, c[K], D.r, c[K - 1], D.ya, 0, 0.0, 0, st));
     const TH* y = D.ya;
@@ -1185,7 +1329,8 @@ struct Engine final : EngineBase {
     return MG_OK;
   }
 
-  // u = (uz ? 0 : u) + Phi_P(P ec);  xbuf receives P ec when K >= 1
+  // u = (uz ? 0 : u) + Phi_P(P ec);  xbuf receives P ec when K >= 1, unless it is the level's
+  // scratch vector x and the prolongation runs within the convolution
   mg_status prolong(int l, const TU* ec, TU* u, int uz, TH* xbuf, hipStream_t st) {
     const DL& D = d[l];
     if (pl.KP == 0) {
@@ -1193,6 +1338,10 @@ struct Engine final : EngineBase {
             ROWS_LAUNCH(D, k_prolong, (C, TU, TU), D.P, B(), lbs, ec, u, 1,
                                (C)cP(l)[0], uz));
       return MG_OK;
+    }
+    if constexpr (std::is_same<TH, TU>::value) {
+      if (patched(l, pl.KP) && xbuf == D.x && ec != u)
+        return patch<2>(l, cP(l), pl.KP, ec, nullptr, nullptr, uz ? nullptr : u, u, 1, 1.0, st);
     }
     TIMED(MG_KF_PROLONG, nB(l + 1) * sizeof(TU) + bytes_X(D.P) + nB(l) * sizeof(TH),
           ROWS_LAUNCH(D, k_prolong, (C, TU, TH), D.P, B(), lbs, ec, xbuf, 0,
@@ -1212,6 +1361,9 @@ struct Engine final : EngineBase {
   mg_status fwd(int l, const TU* f, TU* u, int uz, const Ck* ck, hipStream_t st) {
     if (in_tail(l, uz, ck != nullptr)) return run_tail(l, f, u, st, uz, ck);
     if (l == pl.J - 1) return coarse(f, u, 0, st);
+    if constexpr (std::is_same<TH, TU>::value) {
+      if (patched(l, pl.KB) && !pl.nv) return fwd_patch(l, f, u, uz, ck, st);
+    }
     DL& D = d[l];
     for (int j = 0; j < pl.nu_pre; ++j) {
       MG_TRY(smooth(l, f, u, uz, D.s, st, false));
@@ -1224,6 +1376,43 @@ struct Engine final : EngineBase {
     MG_TRY(prolong(l, un, u, uz, D.x, st));
     uz = 0;
     for (int j = 0; j < pl.nu_post; ++j) MG_TRY(smooth(l, f, u, 0, D.s, st));
+    return MG_OK;
+  }
+
+  // fwd on a level with patches: a smoothing step of a nonzero iterate is one launch from one vector to
+  // another, so the iterate alternates between u and the scratch vector s.  It starts where the last step
+  // ends in u: a zero iterate's first step writes either, else the prolongation takes the odd step out.
+  mg_status fwd_patch(int l, const TU* f, TU* u, int uz, const Ck* ck, hipStream_t st) {
+    DL& D = d[l];
+    TU* const buf[2] = {u, D.s};
+    const int steps = pl.nu_post + std::max(0, pl.nu_pre - (uz ? 1 : 0));
+    int at = uz ? steps & 1 : 0;
+    bool odd = !uz && (steps & 1);
+    auto step = [&]() -> mg_status {
+      if (odd && !patched(l, pl.KP)) {   // one step in place
+        odd = false;
+        return smooth(l, f, buf[at], 0, D.x, st);
+      }
+      at ^= 1;
+      return patch<1>(l, cB(l), pl.KB, f, buf[at ^ 1], D.L.invdiag, buf[at ^ 1], buf[at], 1, eta(l) * theta(l), st);
+    };
+    for (int j = 0; j < pl.nu_pre; ++j) {
+      if (uz) MG_TRY(smooth(l, f, buf[at], 1, D.x, st, false));
+      else MG_TRY(step());
+      uz = 0;
+    }
+    TU* fn = ck ? ck->f[l + 1] : d[l + 1].f;
+    TU* un = ck ? ck->u[l + 1] : d[l + 1].u;
+    MG_TRY(restrict_(l, f, buf[at], uz, fn, st));
+    MG_TRY(fwd(l + 1, fn, un, 1, ck, st));
+    if (odd && patched(l, pl.KP)) {
+      at ^= 1;
+      odd = false;
+      MG_TRY((patch<2>(l, cP(l), pl.KP, un, nullptr, nullptr, buf[at ^ 1], buf[at], 1, 1.0, st)));
+    } else {
+      MG_TRY(prolong(l, un, buf[at], uz, D.x, st));
+    }
+    for (int j = 0; j < pl.nu_post; ++j) MG_TRY(step());
     return MG_OK;
   }
 

@@ -1083,4 +1083,12 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_bwd(TailBwdArgs<C> args, 
   }
 }
 
+// The two kernels are the bulk of the device code: each precision is a translation unit of its own
+// (tail_f32.hip, tail_f64.hip), compiled beside the engines'.
+#define MGL_TAIL_KERNELS(EXTERN, C)                                                              \
+  EXTERN template __global__ void k_tail<false, C>(TailArgs<C>, int, const C*, C*, int, int);    \
+  EXTERN template __global__ void k_tail<true, C>(TailArgs<C>, int, const C*, C*, int, int);     \
+  EXTERN template __global__ void k_tail_bwd<false, C>(TailBwdArgs<C>, int, const C*, const C*, C*, C*); \
+  EXTERN template __global__ void k_tail_bwd<true, C>(TailBwdArgs<C>, int, const C*, const C*, C*, C*);
+
 }  // namespace mgl
