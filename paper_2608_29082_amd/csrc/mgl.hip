@@ -1599,9 +1599,7 @@ struct Engine final : EngineBase {
     TU* rc = ckv ? ck.f[0] : r0;
     MG_TRY(outer_resid<TU>(f, uin, nullptr, rc, nullptr, st));
     MG_TRY(fwd(0, rc, e0, 1, ckv ? &ck : nullptr, st));
-    if (uout != uin) MG_TRY(copy(uin, uout, n0B, st));
-    hipLaunchKernelGGL((k_update<TU>), dim3(d[0].blocks), dim3(256), 0, st, pl.lv[0].n, B(), lbs, (const TU*)e0, uout,
-                       (const int*)nullptr, 1.0);
+    hipLaunchKernelGGL((k_update<TU>), dim3(nblocks(n0B)), dim3(256), 0, st, n0B, (const TU*)e0, uin, uout);
     LAUNCH_OK();
     return MG_OK;
   }
