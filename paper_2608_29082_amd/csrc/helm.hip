@@ -199,19 +199,38 @@ __global__ __launch_bounds__(256) void k_hz_hop(GEll G, const T* __restrict__ in
   }
 }
 
-// transfer with feature mixing: v = W (X in)_i; ADD: out += v, else out = v
+// transfer with feature mixing: v = W (X in)_i; ADD: out += v, else out = v; zero (if not null) <- 0 (the
+// coarse iterate of a cycle, whose own launch this saves).  Bound by the latency of its loads: a row's
+// slots, then their vector entries, are issued five at a time (a row of a bilinear restriction has nine,
+// one of its prolongation up to four; more at once costs registers that larger levels need): 3.6 us, the
+// mean over the levels of 129 x 129 x 5 FP64, where one slot after another took 4.4.
 template <class T, bool ADD>
 __global__ __launch_bounds__(256) void k_hz_xfer(REll<T> X, int B, int lb, const cx<T>* __restrict__ in, W2<T> W,
-                                                 cx<T>* __restrict__ out) {
+                                                 cx<T>* __restrict__ out, cx<T>* __restrict__ zero) {
+  constexpr int G = 5;
   HZ_ROW(X.n)
   T ar = 0, ai = 0;
-  for (int s = 0; s < X.w; ++s) {
-    const int j = X.col[(size_t)s * X.n + i];
-    const T a = X.val[(size_t)s * X.n + i];
-    const cx<T> t = in[(size_t)j * B + b];
-    ar += a * t.x;
-    ai += a * t.y;
+  for (int s0 = 0; s0 < X.w; s0 += G) {
+    int j[G];
+    T a[G];
+    cx<T> t[G];
+#pragma unroll
+    for (int s = 0; s < G; ++s)
+      if (s0 + s < X.w) {
+        j[s] = X.col[(size_t)(s0 + s) * X.n + i];
+        a[s] = X.val[(size_t)(s0 + s) * X.n + i];
+      }
+#pragma unroll
+    for (int s = 0; s < G; ++s)
+      if (s0 + s < X.w) t[s] = in[(size_t)j[s] * B + b];
+#pragma unroll
+    for (int s = 0; s < G; ++s)
+      if (s0 + s < X.w) {
+        ar += a[s] * t[s].x;
+        ai += a[s] * t[s].y;
+      }
   }
+  if (zero) zero[o] = mkc<T>(0, 0);
   const cx<T> v = mixw(W, mkc<T>(ar, ai));
   if (ADD) {
     cx<T> u = out[o];
@@ -1568,16 +1587,18 @@ struct HzEngine final : mgh_ctx {
     return MG_OK;
   }
 
-  // r_{l+1} = R_l Phi_R(x) into F[l+1]
-  mg_status restrict_(int l, const cx<T>* x, hipStream_t st) {
+  // r_{l+1} = R_l Phi_R(x) into F[l+1]; zu (if not null): n_{l+1} x B entries set to zero
+  mg_status restrict_(int l, const cx<T>* x, cx<T>* zu, hipStream_t st) {
     Lv& L = lv[l];
     Lv& C = lv[l + 1];
     const dim3 g(rows_grid(C.n));
     if (KR == 0) {
-      hipLaunchKernelGGL((k_hz_xfer<T, false>), g, dim3(256), 0, st, L.R, Bn, lb, x, WR.w[0], C.F);
+      hipLaunchKernelGGL((k_hz_xfer<T, false>), g, dim3(256), 0, st, L.R, Bn, lb, x, WR.w[0], C.F,
+                         zu);
     } else {
       H_TRY(conv(l, WR, KR, x, L.D, (T)1, false, st));
-      hipLaunchKernelGGL((k_hz_xfer<T, false>), g, dim3(256), 0, st, L.R, Bn, lb, (const cx<T>*)L.D, eye(), C.F);
+      hipLaunchKernelGGL((k_hz_xfer<T, false>), g, dim3(256), 0, st, L.R, Bn, lb, (const cx<T>*)L.D, eye(), C.F,
+                         zu);
     }
     H_LAUNCH();
     return MG_OK;
@@ -1587,13 +1608,14 @@ struct HzEngine final : mgh_ctx {
     Lv& L = lv[l];
     const dim3 g(rows_grid(L.n));
     const cx<T>* ec = lv[l + 1].U;
+    cx<T>* const nz = nullptr;
     if (KP == 0) {
-      if (add) hipLaunchKernelGGL((k_hz_xfer<T, true>), g, dim3(256), 0, st, L.P, Bn, lb, ec, WP.w[0], out);
-      else hipLaunchKernelGGL((k_hz_xfer<T, false>), g, dim3(256), 0, st, L.P, Bn, lb, ec, WP.w[0], out);
+      if (add) hipLaunchKernelGGL((k_hz_xfer<T, true>), g, dim3(256), 0, st, L.P, Bn, lb, ec, WP.w[0], out, nz);
+      else hipLaunchKernelGGL((k_hz_xfer<T, false>), g, dim3(256), 0, st, L.P, Bn, lb, ec, WP.w[0], out, nz);
       H_LAUNCH();
       return MG_OK;
     }
-    hipLaunchKernelGGL((k_hz_xfer<T, false>), g, dim3(256), 0, st, L.P, Bn, lb, ec, eye(), L.Tb);
+    hipLaunchKernelGGL((k_hz_xfer<T, false>), g, dim3(256), 0, st, L.P, Bn, lb, ec, eye(), L.Tb, nz);
     H_LAUNCH();
     return conv(l, WP, KP, L.Tb, out, (T)1, add, st);
   }
@@ -1611,8 +1633,7 @@ struct HzEngine final : mgh_ctx {
     hipLaunchKernelGGL((k_hz_resid<T, false>), dim3(rows_grid(L.n)), dim3(256), 0, st, L.A, Bn, lb, f,
                        (const cx<T>*)u, (const cx<T>*)nullptr, (T)0, L.Rb);
     H_LAUNCH();
-    H_TRY(restrict_(l, L.Rb, st));
-    if (l + 1 < J - 1) H_TRY(zero(lv[l + 1].U, lv[l + 1].n, st));
+    H_TRY(restrict_(l, L.Rb, l + 1 < J - 1 ? lv[l + 1].U : nullptr, st));
     H_TRY(cycle(l + 1, lv[l + 1].F, lv[l + 1].U, st));
     H_TRY(prolong(l, u, true, st));
     for (int s = 0; s < L.post; ++s) H_TRY(smooth(l, f, u, st));
@@ -1638,7 +1659,7 @@ struct HzEngine final : mgh_ctx {
     std::vector<const cx<T>*> fs(J);
     fs[0] = f;
     for (int l = 0; l < J - 1; ++l) {
-      H_TRY(restrict_(l, fs[l], st));
+      H_TRY(restrict_(l, fs[l], nullptr, st));
       fs[l + 1] = lv[l + 1].F;
     }
     H_TRY(coarse(fs[J - 1], lv[J - 1].U, st));
