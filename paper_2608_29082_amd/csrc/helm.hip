@@ -634,9 +634,9 @@ __global__ __launch_bounds__(MODE == 1 ? kGT : kGTH) void k_hz_gmres(CEll<T> A, 
 }
 
 // ------------------------------------------------------------------ GMRES smoothing step, rows in registers
-// The same step for levels of at most 1536 rows with each work-item's rows (1 or
-// 3 of them, row r of work-item t being t + r * 512) in registers: A's rows, r,
-// d0, u and the basis vectors.  Only what neighbours read is in LDS: the vector a
+// The same step for levels of at most 1536 rows (4608 in FP32, gmres_fn) with each
+// work-item's rows (1, 3 or 9 of them, row r of work-item t being t + r * 512) in
+// registers: A's rows (not with 9), r, d0, u and the basis vectors.  Only what neighbours read is in LDS: the vector a
 // sparse product gathers, in two buffers used in turn, so a product costs one
 // barrier and the Gram-Schmidt sweeps none.
 //
@@ -766,16 +766,21 @@ __global__ __launch_bounds__(kGR) void k_hz_gmres_r(CEll<T> A, GEll G, const T* 
   }
   // slot q of an ELL array: a uniform base, so that a row's loads share one offset register
   auto slot = [&](auto* p, int q, int w) __attribute__((always_inline)) { return p + (size_t)(q < w ? q : 0) * n; };
-  int ac[RPT][W];
-  cx<T> av[RPT][W];
-#pragma unroll
-  for (int r = 0; r < RPT; ++r)
+  constexpr bool KEEP = RPT <= 3;  // A's rows in registers, else read (from the L2) for each product
+  int ac[KEEP ? RPT : 1][W];
+  cx<T> av[KEEP ? RPT : 1][W];
+  auto row = [&](unsigned i, int (&c)[W], cx<T> (&a)[W]) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < W; ++q) {   // slots past the width repeat the first column with value 0
-      ac[r][q] = slot(A.col, q, A.w)[ic[r]];
-      av[r][q] = slot(A.val, q, A.w)[ic[r]];
-      if (q >= A.w) av[r][q] = mkc<T>(0, 0);
+      c[q] = slot(A.col, q, A.w)[i];
+      a[q] = slot(A.val, q, A.w)[i];
+      if (q >= A.w) a[q] = mkc<T>(0, 0);
     }
+  };
+  if constexpr (KEEP) {
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) row(ic[r], ac[r], av[r]);
+  }
   cx<T> R[RPT], D0[RPT], w[RPT], V[kGRv][RPT];
   auto store = [&](const cx<T> (&z)[RPT]) __attribute__((always_inline)) {
 #pragma unroll
@@ -785,16 +790,23 @@ __global__ __launch_bounds__(kGR) void k_hz_gmres_r(CEll<T> A, GEll G, const T* 
   // z = A x with x at lds + cur
   auto amul = [&](cx<T> (&z)[RPT]) __attribute__((always_inline)) {
     const cx<T>* x = lds + cur;
+    unsigned z0 = 0;
+    if constexpr (!KEEP) asm volatile("" : "+s"(z0));   // unknown to the compiler: no row is kept to the next product
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
       cx<T> t[W];
+      const int k = KEEP ? r : 0;
+      if constexpr (!KEEP) {
+        if (r % 2 == 0) __builtin_amdgcn_sched_barrier(0);   // two rows' loads in flight, not nine
+        row(ic[r] + z0, ac[0], av[0]);
+      }
 #pragma unroll
-      for (int q = 0; q < W; ++q) t[q] = x[ac[r][q]];
+      for (int q = 0; q < W; ++q) t[q] = x[ac[k][q]];
       T ar = 0, ai = 0;
 #pragma unroll
       for (int q = 0; q < W; ++q) {
-        ar += av[r][q].x * t[q].x - av[r][q].y * t[q].y;
-        ai += av[r][q].x * t[q].y + av[r][q].y * t[q].x;
+        ar += av[k][q].x * t[q].x - av[k][q].y * t[q].y;
+        ai += av[k][q].x * t[q].y + av[k][q].y * t[q].x;
       }
       z[r] = mkc<T>(ar, ai);
     }
@@ -1443,11 +1455,15 @@ template <class T>
 struct HzEngine final : mgh_ctx {
   using GmresFn = void (*)(CEll<T>, GEll, const T*, int, const cx<T>*, cx<T>*, T, T, WK<T>, int, int);
   // The GMRES smoothing step with rows in registers for a level of n rows of w slots (null: the sweep
-  // form, for more than kGRv steps, wider rows, or more than three rows per work-item: with nine, or
-  // five of 1024, A's rows no longer fit the registers and reading them again in every product took
-  // FP32 65 x 65 levels from 145 to 100 us but FP64 ones from 208 to 225)
+  // form, for more than kGRv steps, wider rows, or more than three rows per work-item).  Nine rows
+  // do not leave registers for A's, which each product reads again from the L2: FP32 65 x 65 levels
+  // (x 16) go from 145 to 90 us, FP64 ones from 208 to 225, so FP32 only, and only where at least two
+  // thirds of the nine are rows
   static GmresFn gmres_fn(int n, int w, int v) {
-    if (v > kGRv || w > kGRw || w < 1 || n > 3 * kGR) return nullptr;
+    if (v > kGRv || w > kGRw || w < 1) return nullptr;
+    if constexpr (std::is_same<T, float>::value)
+      if (w <= 7 && n > 6 * kGR && n <= 9 * kGR) return &k_hz_gmres_r<T, 9, 7>;
+    if (n > 3 * kGR) return nullptr;
     if (n <= kGR) return w <= 7 ? &k_hz_gmres_r<T, 1, 7> : &k_hz_gmres_r<T, 1, 8>;
     return w <= 7 ? &k_hz_gmres_r<T, 3, 7> : &k_hz_gmres_r<T, 3, 8>;
   }
@@ -2030,7 +2046,7 @@ struct HzEngine final : mgh_ctx {
           const size_t all = (size_t)hz_slots(v) * n * sizeof(cx<T>), basis = (size_t)v * n * sizeof(cx<T>);
           L.gfn = gmres_fn(n, w, v);
           if (L.gfn) {
-            L.lds = 2 * (size_t)n * sizeof(cx<T>);   // at most 48 KB
+            L.lds = 2 * (size_t)n * sizeof(cx<T>);   // at most 72 KB
           } else if (all <= (size_t)kGmresLds) {
             L.gmode = 1;
             L.lds = all;
@@ -2126,6 +2142,9 @@ struct HzEngine final : mgh_ctx {
                               hipFuncAttributeMaxDynamicSharedMemorySize, kGmresLds));
     H_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hz_gmres<T, 2>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, kGmresLds));
+    if constexpr (std::is_same<T, float>::value)
+      H_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hz_gmres_r<T, 9, 7>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kGmresLds));
     H_HIP(hipHostMalloc((void**)&hcnt, sizeof(int)));
     H_HIP(hipStreamSynchronize(st));
     return MG_OK;
