@@ -1407,8 +1407,8 @@ static __global__ void k_solve_check(const double* __restrict__ norms, double* _
   if (threadIdx.x == 0) st[3 * B] = cnt[0];
 }
 
-// out = u + e (out may be u).  Bound by its 8 + sizeof(TU) bytes in and 8 out an entry: 57 us on
-// 511 x 511 x 64 with FP32 e (5.8 TB/s), where a copy of u and an update in place took 104.
+// out = u + e (out may be u).  Bound by its 8 + sizeof(TU) bytes in and 8 out an entry: 50 us on
+// 511 x 511 x 64 with FP32 e (6.6 TB/s), where a copy of u and an update in place took 104.
 template <class TU>
 __global__ __launch_bounds__(256) void k_update(long cnt, const TU* __restrict__ e, const double* u, double* out) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1776,7 +1776,7 @@ static __global__ __launch_bounds__(256) void k_dots_final(const Sum2* __restric
 }
 
 // Parameter gradients from the dot products: one work-item per parameter, each adding the slots that
-// belong to it in slot order (12 us at 150 slots; one work-item adding all of them took 61).
+// belong to it in slot order (12 us at 150 slots, 26 at 290; one work-item adding all of the 150 took 61).
 // desc[s] = {kind (0 smoother, 1 restriction, 2 prolongation), level, k}.
 // Smoother dot e = <(M^T)^k g, s> with s = D^{-1}(f - A u):
 //   dc_k += eta theta e,  deta += theta c_k e,  dtheta += eta c_k e.
