@@ -694,16 +694,19 @@ struct Engine final : EngineBase {
     auto fits = [&](int lt) {
       if (lt < 0 || J - lt > kTailMaxLevels) return false;
       long old = 4 * r4(pl.lv[lt].n);
-      for (int l = lt; l < J; ++l) {
-        old += 2 * r4(pl.lv[l].n);
-        if (l < J - 1 && !wu[l]) variant(l);
-      }
+      for (int l = lt; l < J; ++l) old += 2 * r4(pl.lv[l].n);
+      if (!d[lt].td.ntiles && (size_t)old * sizeof(C) > (size_t)maxlds) return false;
       TailArgs<C> t = proto;
-      for (int l = lt; l < J - 1; ++l) t.lv[l - lt].rpt = rpt[l];
-      return (d[lt].td.ntiles || (size_t)old * sizeof(C) <= (size_t)maxlds) && tail_layout(lt, t) <= (size_t)maxlds;
+      for (int l = lt; l < J - 1; ++l) {
+        if (!wu[l]) variant(l);
+        t.lv[l - lt].rpt = rpt[l];
+      }
+      return tail_layout(lt, t) <= (size_t)maxlds;
     };
-    int lt = J - 1;
-    while (lt > 0 && d[lt - 1].td.ntiles == 0 && pl.lv[lt - 1].n <= 65536 && fits(lt - 1)) --lt;
+    // the first such level, whatever lies below it: a level without tiles (its rows too wide for their LDS)
+    // can have tiled levels below it
+    int lt = 0;
+    while (lt < J - 1 && (d[lt].td.ntiles != 0 || !fits(lt))) ++lt;
     tail_own = lt;
     if (std::is_same<TH, TU>::value && pl.KR >= 1 && lt > 1 && lt < J && d[lt - 1].td.ntiles && fits(lt - 1) &&
         rpt[lt - 1] != 0)

@@ -1,0 +1,32 @@
+"""Which levels the coarse tail holds."""
+import pytest
+
+from mginputs import configs as C
+from tests.gpu_util import to_dev
+from tests.test_gpu_tail import _hierarchy
+
+pytestmark = pytest.mark.gpu
+
+
+def _launches(family, level, prec, **kw):
+    """Launches of one kernel family on one level of a cycle: 5000 rows with ten neighbours each, too wide
+    for tiles, over 2500 rows with two."""
+    from paper_2608_29082_amd import binding as Bd
+    import torch
+    A, P = _hierarchy(5000, 10, 3)
+    J, K, B = len(A), 3, 16
+    ctx = Bd.Context(A, P, C.random_params(J, K, K, K, seed=5, spread=0.1), K, K, K, precision=prec, nrhs=B, **kw)
+    f = to_dev(C.rng(11, 7, 0).standard_normal((5000, B)), torch.float64)
+    ctx.timing_start(family, level)
+    ctx.refine_step(f, torch.zeros_like(f))
+    n = ctx.timing_read()[0]
+    ctx.close()
+    return n
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_tiled_level_below_an_untiled_one_stays_in_the_tail(prec):
+    """The tail starts at the finest level without tiles that fits its LDS and holds every level below it:
+    here the whole cycle, also the 2500 rows that have tiles (BF16 cycles keep FP32 vectors in it)."""
+    assert _launches("hop", 0, "bf16", tail=False) > 0 and _launches("conv", 1, prec, tail=False) > 0
+    assert _launches("conv", -1, prec) == 0 and _launches("resid", -1, prec) == 0
