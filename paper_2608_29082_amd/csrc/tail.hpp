@@ -330,6 +330,14 @@ struct TailXfer2 {
     }
   }
 };
+// s + w t for a slot of a restriction's row (nothing for weight 0).  The per-level sweep (k_restrict)
+// rounds the product, the tail's own sum does not: `ord` as in tail_resid.
+template <class C>
+__device__ __forceinline__ C tail_rsum(C s, C w, C t, bool on, int ord) {
+#pragma clang fp contract(off)
+  const C m = s + w * t;
+  return on && w != C(0) ? (ord ? m : tfma(w, t, s)) : s;
+}
 // out[i] = (X v)_i for a transfer X to at most n_c rows; v at LDS address src.  The row's slots can be
 // loaded ahead (pre)
 template <bool PF, class C>
@@ -352,7 +360,7 @@ struct TailXfer8 {
       }
     }
   }
-  __device__ __forceinline__ void apply(const Xfer<C>& X, int nt, uint32_t src, C* out) const {
+  __device__ __forceinline__ void apply(const Xfer<C>& X, int nt, uint32_t src, C* out, int ord) const {
     const int tid = threadIdx.x;
     if (pre) {
       if constexpr (PF) {
@@ -361,7 +369,7 @@ struct TailXfer8 {
 #pragma unroll
           for (int k = 0; k < kTailW; ++k) t[k] = lds_get<C>(src + j[k] * (uint32_t)sizeof(C));
 #pragma unroll
-          for (int k = 0; k < kTailW; ++k) g = k < X.w && w[k] != C(0) ? tfma(w[k], t[k], g) : g;
+          for (int k = 0; k < kTailW; ++k) g = tail_rsum(g, w[k], t[k], k < X.w, ord);
           if (tid < X.n) out[tid] = g;
         }
       }
@@ -380,7 +388,7 @@ struct TailXfer8 {
 #pragma unroll
           for (int k = 0; k < kTailW; ++k) t[k] = lds_get<C>(src + jj[k] * (uint32_t)sizeof(C));
 #pragma unroll
-          for (int k = 0; k < kTailW; ++k) g = k0 + k < X.w && ww[k] != C(0) ? tfma(ww[k], t[k], g) : g;
+          for (int k = 0; k < kTailW; ++k) g = tail_rsum(g, ww[k], t[k], k0 + k < X.w, ord);
         }
         out[e] = g;
       }
@@ -463,7 +471,7 @@ __device__ __forceinline__ void tail_visit(const TailArgs<C>& T, C* sm, uint32_t
     }
     M.store(out, v);
     tail_sync<WAVE>();
-    R.apply(tl.R, Rows::nt, wk + out, sm + T.lv[q + 1].off_f);
+    R.apply(tl.R, Rows::nt, wk + out, sm + T.lv[q + 1].off_f, M.ord);
   }
   tail_sync<WAVE>();
 }
@@ -538,12 +546,12 @@ __device__ __forceinline__ void tl_hop(const Lvl<C>& L, const C* yin, C a, const
 
 // out = X v  for an ELL transfer X (rows X.n)
 template <class C>
-__device__ __forceinline__ void tl_xfer(const Xfer<C>& X, const C* v, C* out) {
+__device__ __forceinline__ void tl_xfer(const Xfer<C>& X, const C* v, C* out, int ord) {
   for (int i = threadIdx.x; i < X.n; i += kTailThreads) {
     C s = C(0);
     for (int k = 0; k < X.w; ++k) {
       const C w = X.val[(size_t)k * X.n + i];
-      s = w != C(0) ? tfma(w, v[X.col[(size_t)k * X.n + i]], s) : s;
+      s = tail_rsum(s, w, v[X.col[(size_t)k * X.n + i]], true, ord);
     }
     out[i] = s;
   }
@@ -582,7 +590,7 @@ __device__ __forceinline__ void tail_visit_generic(const TailArgs<C>& T, C* sm, 
   const C* p = prm + q * T.per;
   const C *cB = p + 2, *cR = cB + T.KB + 1, *cP = cR + T.KR + 1;
   if (what & (TV_PRO | TV_PRO_SET)) {
-    tl_xfer(tl.P, sm + T.lv[q + 1].off_u, X);
+    tl_xfer(tl.P, sm + T.lv[q + 1].off_u, X, 0);
     tl_conv_add<WG>(L, cP, T.KP, X, C(1), cP[0], U, (what & TV_PRO_SET) ? 1 : uz, S, Y, ord);
     uz = 0;
   }
@@ -602,7 +610,7 @@ __device__ __forceinline__ void tail_visit_generic(const TailArgs<C>& T, C* sm, 
       }
     }
     tl_conv_add<WG>(L, cR, T.KR, x, C(1), cR[0], Z, 1, S, Y, ord);
-    tl_xfer(tl.R, Z, sm + T.lv[q + 1].off_f);
+    tl_xfer(tl.R, Z, sm + T.lv[q + 1].off_f, ord);
   }
 }
 
@@ -976,7 +984,7 @@ __device__ __forceinline__ void tail_bwd_visit(const TailBwdArgs<C>& A, C* sm, u
     tail_sync<WAVE>();
     TailXfer8<false, C> R;
     R.load(tb.PT, Rows::nt, false);
-    R.apply(tb.PT, Rows::nt, wk + out, sm + T.lv[q + 1].off_u);
+    R.apply(tb.PT, Rows::nt, wk + out, sm + T.lv[q + 1].off_u, 0);   // (by k_prolong level by level)
   } else {
     TailXfer2<RPT, C> P;
     if (M.act) P.load(tb.RT, M.ic);

@@ -30,3 +30,29 @@ def test_tiled_level_below_an_untiled_one_stays_in_the_tail(prec):
     here the whole cycle, also the 2500 rows that have tiles (BF16 cycles keep FP32 vectors in it)."""
     assert _launches("hop", 0, "bf16", tail=False) > 0 and _launches("conv", 1, prec, tail=False) > 0
     assert _launches("conv", -1, prec) == 0 and _launches("resid", -1, prec) == 0
+
+
+@pytest.mark.parametrize("prec,n,width", [("fp32", 60, 6), ("fp32", 900, 6), ("fp32", 1300, 10), ("fp32", 4000, 8),
+                                          ("fp64", 900, 6), ("fp64", 2100, 4)])
+def test_restriction_in_the_tail_rounds_as_the_sweeps(prec, n, width):
+    """With restriction weights whose products are rounded (0.9 P^T), a step that records a checkpoint still
+    carries the bits of the per-level sweeps, and so do its gradients."""
+    import numpy as np
+    import scipy.sparse as sp
+    import torch
+    from paper_2608_29082_amd import binding as Bd
+    from tests.gpu_util import to_np
+    A, P = _hierarchy(n, width, n)
+    J, K, B = len(A), 2, 3
+    flat = C.random_params(J, K, K, K, seed=n, spread=0.2)
+    g = C.rng(11, 8, n)
+    f, u = (to_dev(g.standard_normal((n, B)), torch.float64) for _ in range(2))
+    outs = []
+    for tail in (True, False):
+        ctx = Bd.Context(A, P, flat, K, K, K, precision=prec, nrhs=B, tail=tail, tiles=False, backward=True,
+                         R=[sp.csr_matrix(0.9 * p.T) for p in P])
+        ck = ctx.new_ckpt()
+        step = ctx.refine_step(f, u, ckpt=ck)
+        outs.append([to_np(step)] + [to_np(t) for t in ctx.refine_step_backward(ck, f)[:2]])
+        ctx.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*outs))
