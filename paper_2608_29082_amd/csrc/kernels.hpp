@@ -1638,9 +1638,10 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_chain_tile(TileDev T, int B
     for (int e = 0; e < kTileOwnPerThread; ++e)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        sv[e][c] = bc.ov[e][c];               // zero on rows that are not the tile's own
+        sv[e][c] = bc.ov[e][c];
         acc[e][c] = cf.c[0] * bc.xv[e][c];
-        d = sum2_add(d, (double)bc.xv[e][c] * (double)sv[e][c]);
+        // (rows that are not the tile's own add nothing, also where x is infinite)
+        if (p0 + e * kTileNp < h.own) d = sum2_add(d, (double)bc.xv[e][c] * (double)sv[e][c]);
       }
 #pragma unroll
     for (int e = 0; e < kTileRows; ++e) {
@@ -1686,7 +1687,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_chain_tile(TileDev T, int B
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
               acc[e][c] = hop_update(acc[e][c], ck, z[c]);
-              d = sum2_add(d, (double)z[c] * (double)sv[e][c]);
+              if (r < h.own) d = sum2_add(d, (double)z[c] * (double)sv[e][c]);
             }
           }
           if (hp < K) {
@@ -1771,7 +1772,7 @@ static __global__ __launch_bounds__(256) void k_dots_final(const Sum2* __restric
   __syncthreads();
   if (threadIdx.x == 0) {
     v = sum2_add(sum2_add(red[0], red[1]), sum2_add(red[2], red[3]));
-    dots[s] = v.hi + v.lo;
+    dots[s] = sum2_value(v);
   }
 }
 

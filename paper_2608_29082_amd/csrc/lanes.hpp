@@ -51,6 +51,9 @@ __device__ __forceinline__ double wave_sum(double v) {
 struct Sum2 {
   double hi, lo;
 };
+// The sum, rounded.  hi is the plain FP64 sum of the terms; once it is infinite or NaN its error term lo is
+// NaN, and hi alone is the result.
+__device__ __forceinline__ double sum2_value(Sum2 s) { return __builtin_isfinite(s.lo) ? s.hi + s.lo : s.hi; }
 // s + v (Knuth's two-sum; the error of hi goes to lo)
 __device__ __forceinline__ Sum2 sum2_add(Sum2 s, double v) {
   const double h = s.hi + v, t = h - s.hi;
