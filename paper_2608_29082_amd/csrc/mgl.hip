@@ -2110,8 +2110,11 @@ struct Engine final : EngineBase {
     if (!ckv || !goutv) return fail(MG_ERR_INVALID_ARG, "checkpoint and gu_out are required");
     Ck ck = ck_ptrs(const_cast<void*>(ckv));
     slot = 0;
-    TU* gf = gfv ? static_cast<TU*>(gfv) : d[0].gfo;
+    // transposed convolutions over tiles add to gf in units of 16 bytes
+    const bool direct = gfv && (d[0].td.ntiles == 0 || (uintptr_t)gfv % 16 == 0);
+    TU* gf = direct ? static_cast<TU*>(gfv) : d[0].gfo;
     MG_TRY(bwd_level(0, ck.f[0], ck.u[0], static_cast<const TU*>(goutv), gf, static_cast<TU*>(ginv), ck, st));
+    if (gfv && !direct) MG_TRY(copy((const TU*)gf, static_cast<TU*>(gfv), (long)pl.lv[0].n * B(), st));
     return finish_grads(gp, st);
   }
 
