@@ -2025,12 +2025,13 @@ struct Engine final : EngineBase {
         a.b[q].f = ck.f[l + q];
         a.b[q].ec = ck.u[l + q + 1];
       }
-      if (slot + a.T.nl - 1 > nslots) return fail(MG_ERR_STATE, "reverse sweep slot overflow");
+      const int used = (a.T.nl - 1) * (slots_down() + slots_up());
+      if (slot + used > nslots) return fail(MG_ERR_STATE, "reverse sweep slot overflow");
       a.part = dpart + h_off[slot];
       WG_SPLIT(hipLaunchKernelGGL((k_tail_bwd<WGv, C>), dim3(B()), dim3(kTailThreads), btail_bytes, st, a, B(), uin,
                                   gout, gfl, gul));
       LAUNCH_OK();
-      slot += (a.T.nl - 1) * (slots_down() + slots_up());
+      slot += used;
       return MG_OK;
     }
     DL& D = d[l];
