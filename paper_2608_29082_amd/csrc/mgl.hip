@@ -14,9 +14,11 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
+#include <future>
 #include <memory>
 #include <mutex>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <type_traits>
 #include <vector>
@@ -159,6 +161,8 @@ struct EngineBase {
   std::vector<hipEvent_t> tev;   // start/stop pairs, reused across runs
   size_t tn = 0;                 // pairs recorded
   double tbytes = 0.0;
+  // level l of the host plan is complete (called while the plan's other levels are still built)
+  virtual void level_built(int) {}
   virtual ~EngineBase() {
     for (hipEvent_t e : tev) (void)hipEventDestroy(e);
   }
@@ -537,6 +541,10 @@ struct Engine final : EngineBase {
     HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&hcount), sizeof(int) * 4, hipHostMallocDefault));
     HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&hmap), sizeof(int) * 3 * pl.B, hipHostMallocDefault));
     const int J = pl.J;
+    // what runs each level depends on the plan and the workspace's addresses only
+    MG_TRY(setup_tiles(st));
+    MG_TRY(setup_tail());
+    if (bwd()) MG_TRY(setup_bwd_tail());
     for (int l = 0; l < J; ++l) {
       const HLevel& H = pl.lv[l];
       DL& x = d[l];
@@ -601,26 +609,21 @@ struct Engine final : EngineBase {
       }
     }
     MG_TRY(up(dprm, pl.params, st));
-    int info = 0;
-    HIP_TRY(hipMemcpyAsync(hcount, dinfo, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    info = hcount[0];
-    staging.clear();
-    staging.shrink_to_fit();
-    if (info != 0) return fail(MG_ERR_SHAPE, "coarsest matrix is singular (zero pivot in column " + std::to_string(info - 1) + ")");
-    MG_TRY(setup_tiles(st));
-    MG_TRY(setup_tail());
-    if (!bwd()) MG_TRY(setup_patches(st));
+    MG_TRY(setup_patches(st));
     if (bwd()) {
-      MG_TRY(setup_bwd_tail());
-      MG_TRY(setup_patches(st));
       h_off.clear(); h_cnt.clear(); h_desc.clear();
       enum_slots(0, false);
       HIP_TRY(hipMemcpyAsync(doff, h_off.data(), h_off.size() * sizeof(long), hipMemcpyHostToDevice, st));
       MG_TRY(upi(dcnt, h_cnt, st));
       MG_TRY(upi(ddesc, h_desc, st));
-      HIP_TRY(hipStreamSynchronize(st));
     }
+    HIP_TRY(hipMemcpyAsync(hcount, dinfo, sizeof(int), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    const int info = hcount[0];
+    staging.clear();
+    staging.shrink_to_fit();
+    patch_host.clear();
+    if (info != 0) return fail(MG_ERR_SHAPE, "coarsest matrix is singular (zero pivot in column " + std::to_string(info - 1) + ")");
     sizes.resize(J);
     widths.resize(J);
     for (int l = 0; l < J; ++l) { sizes[l] = pl.lv[l].n; widths[l] = pl.lv[l].off.w; }
@@ -964,64 +967,113 @@ struct Engine final : EngineBase {
   }
 
   // Patches of the levels above the coarse tail that have no tiles (k_patch): for FP64 cycles and for
-  // FP32 with widths that are no multiple of kTileCols, up to patch_limit entries.  Not with BF16 intermediates, which the
-  // per-hop sweeps round.  The patch lists take about 30 bytes a node.
-  mg_status setup_patches(hipStream_t st) {
-    if (!std::is_same<TH, TU>::value || (pl.flags & MG_FLAG_NO_TILES)) return MG_OK;
+  // FP32 with widths that are no multiple of kTileCols, up to patch_limit entries.  Not with BF16
+  // intermediates, which the per-hop sweeps round.
+  // The lists (36 bytes a node of a 5-point or 7-point grid with K = 3) are built on the host, a level's on
+  // threads of its own from the moment its graph is known, beside the rest of the plan and the uploads.
+  // A setup with patches / with them built after the uploads / without patches takes 1.2 / 1.65 / 1.0 ms on
+  // 129 x 129 x 1, 3.8 / 5.7 / 3.4 on 257 x 257 x 1 and 15.7 / 24 / 15.5 on 513 x 513 x 1.  Two threads a
+  // level: eight are no sooner done than the uploads, and slow down setups that run at the same time (four at
+  // once on 257 x 257 x 1: 1.4 ms a setup with two, 1.6 with eight, 1.2 without patches).
+  static constexpr int kPatchHost = 2;
+  int patch_order() const {          // largest order with patches (0: none)
+    if (!std::is_same<TH, TU>::value || (pl.flags & MG_FLAG_NO_TILES)) return 0;
     int KM = 0;
     for (int K : {pl.KB, pl.KR, pl.KP})
       if (K >= 2) KM = std::max(KM, K);
-    if (KM < 2 || KM > kTileMaxK) return MG_OK;
+    return KM <= kTileMaxK ? KM : 0;
+  }
+  bool patch_level(int l) const {
+    const int KM = patch_order();
+    return KM && l < pl.J - 1 && pl.lv[l].n >= kTileMinRows && (long)pl.lv[l].n * pl.B <= patch_limit(KM);
+  }
+  struct PatchLists {
+    int ntiles = 0, wg = 0;          // ntiles == 0: no patches
+    bool ok = true;                  // the lists pass check_tiles
+    std::vector<int> maxcnt;
+    size_t at[5] = {}, bytes = 0;    // toff, goff, node, cnt, lcol in mem
+    RawVec<char> mem;
+  };
+  PatchLists plan_patches(int l) const {
+    const HLevel& H = pl.lv[l];
+    const HEll& g = H.graph_is_A ? H.off : H.graph;
+    const int KM = patch_order();
+    TilePlan t;
+    // 12 x 12 nodes: a cycle on 257^2 x 1 takes 6.7 / 7.0 / 7.0 ms a solve with sides of 12 / 8 / 16,
+    // one on 385^2 x 7 FP64 590 / 704 / 607 us
+    for (int side : {12, 8, 6, 4}) {
+      if (build_tiles(H.n, g.ld, g.w, g.col.data(), KM, side, side, t, MGL_TILE_GROUP, kPatchHost) &&
+          t.maxcnt[KM - 1] <= kPatchThreads && t.maxcnt[KM] <= 2 * kPatchThreads &&
+          patch_lds(t.maxcnt.data(), KM, 4) <= 65536)
+        break;
+      t = TilePlan{};
+    }
+    PatchLists p;
+    if (!t.ntiles) return p;
+    p.ntiles = t.ntiles;
+    p.wg = t.wg;
+    p.maxcnt = t.maxcnt;
+    p.ok = check_tiles(H.n, g.ld, g.col.data(), t, kPatchHost);
+    const std::pair<const void*, size_t> part[5] = {{t.toff.data(), t.toff.size() * sizeof(int)},
+                                                    {t.goff.data(), t.goff.size() * sizeof(int)},
+                                                    {t.node.data(), t.node.size() * sizeof(int)},
+                                                    {t.cnt.data(), t.cnt.size() * sizeof(int)},
+                                                    {t.lcol.data(), t.lcol.size() * sizeof(uint16_t)}};
+    for (int k = 0; k < 5; ++k) {
+      p.at[k] = p.bytes;
+      p.bytes += (part[k].second + 255) & ~size_t(255);
+    }
+    p.mem.resize(p.bytes);
+    for (int k = 0; k < 5; ++k) std::memcpy(p.mem.data() + p.at[k], part[k].first, part[k].second);
+    return p;
+  }
+  std::vector<std::future<PatchLists>> patch_jobs;  // per level (waits for its threads when it goes)
+  std::vector<PatchLists> patch_host;               // the lists until their uploads have ended
+  void level_built(int l) override {
+    patch_jobs.resize(pl.J);
+    // Levels that get tiles, or that the coarse tail holds, are known only in the setup; these it builds
+    // itself should they need patches after all.
+    const bool tiles = std::is_same<C, float>::value && pl.B % kTileCols == 0;
+    const bool tail = !(pl.flags & MG_FLAG_NO_TAIL) && pl.lv[l].n <= tail_max_rpt<C>() * kTailThreads;
+    if (tiles || tail || !patch_level(l)) return;
+    try {
+      patch_jobs[l] = std::async(std::launch::async, [this, l] { return plan_patches(l); });
+    } catch (const std::system_error&) {   // no thread to be had: likewise
+    }
+  }
+  mg_status setup_patches(hipStream_t st) {
     const int J = pl.J;
     int lt = tail_lt >= 0 ? tail_lt : J - 1;
     if (bwd()) lt = std::max(lt, btail_lt >= 0 ? btail_lt : J - 1);
-    std::vector<TilePlan> tp(J);
+    patch_host.resize(J);
     size_t bytes = 0;
-    auto a256 = [](size_t b) { return (std::max<size_t>(b, 1) + 255) & ~size_t(255); };
-    for (int l = 0; l < std::min(lt, J - 1); ++l) {
-      const HLevel& H = pl.lv[l];
-      if (H.n < kTileMinRows || d[l].td.ntiles || (long)H.n * pl.B > patch_limit(KM)) continue;
-      const HEll& g = H.graph_is_A ? H.off : H.graph;
-      // 12 x 12 nodes: a cycle on 257^2 x 1 takes 6.7 / 7.0 / 7.0 ms a solve with sides of 12 / 8 / 16,
-      // one on 385^2 x 7 FP64 590 / 704 / 607 us
-      for (int side : {12, 8, 6, 4}) {
-        if (build_tiles(H.n, g.ld, g.w, g.col.data(), KM, side, side, tp[l], MGL_TILE_GROUP) &&
-            tp[l].maxcnt[KM - 1] <= kPatchThreads && tp[l].maxcnt[KM] <= 2 * kPatchThreads &&
-            patch_lds(tp[l].maxcnt.data(), KM, 4) <= 65536)
-          break;
-        tp[l] = TilePlan{};
-      }
-      const TilePlan& t = tp[l];
-      if (!t.ntiles) continue;
-      if (!check_tiles(H.n, g.ld, g.col.data(), t))
-        return fail(MG_ERR_STATE, "patch lists of level " + std::to_string(l) + " are inconsistent");
-      bytes += a256((t.ntiles + 1) * sizeof(int)) * 2 + a256(t.node.size() * sizeof(int)) +
-               a256(t.cnt.size() * sizeof(int)) + a256(t.lcol.size() * sizeof(uint16_t));
+    for (int l = 0; l < J; ++l) {
+      const bool job = l < (int)patch_jobs.size() && patch_jobs[l].valid();
+      PatchLists p;
+      if (job) p = patch_jobs[l].get();
+      if (l >= std::min(lt, J - 1) || d[l].td.ntiles || !patch_level(l)) continue;
+      if (!job) p = plan_patches(l);
+      if (!p.ok) return fail(MG_ERR_STATE, "patch lists of level " + std::to_string(l) + " are inconsistent");
+      bytes += p.bytes;
+      patch_host[l] = std::move(p);
     }
     if (!bytes) return MG_OK;
     HIP_TRY(hipMalloc(&patch_mem, bytes));
-    char* p = patch_mem;
-    bool ok = true;
-    auto put = [&](const void* src, size_t b) -> const void* {
-      void* dst = p;
-      p += a256(b);
-      if (b && hipMemcpyAsync(dst, src, b, hipMemcpyHostToDevice, st) != hipSuccess) ok = false;
-      return dst;
-    };
+    char* dst = patch_mem;
     for (int l = 0; l < J; ++l) {
-      const TilePlan& t = tp[l];
-      if (!t.ntiles) continue;
+      const PatchLists& p = patch_host[l];
+      if (!p.ntiles) continue;
+      HIP_TRY(hipMemcpyAsync(dst, p.mem.data(), p.bytes, hipMemcpyHostToDevice, st));
       PatchDev& v = d[l].pd;
-      v.ntiles = t.ntiles; v.KM = t.KM; v.wg = t.wg;
-      v.toff = static_cast<const int*>(put(t.toff.data(), t.toff.size() * sizeof(int)));
-      v.goff = static_cast<const int*>(put(t.goff.data(), t.goff.size() * sizeof(int)));
-      v.node = static_cast<const int*>(put(t.node.data(), t.node.size() * sizeof(int)));
-      v.cnt = static_cast<const int*>(put(t.cnt.data(), t.cnt.size() * sizeof(int)));
-      v.lcol = static_cast<const uint16_t*>(put(t.lcol.data(), t.lcol.size() * sizeof(uint16_t)));
-      std::copy(t.maxcnt.begin(), t.maxcnt.end(), d[l].pmax);
+      v.ntiles = p.ntiles; v.KM = patch_order(); v.wg = p.wg;
+      v.toff = reinterpret_cast<const int*>(dst + p.at[0]);
+      v.goff = reinterpret_cast<const int*>(dst + p.at[1]);
+      v.node = reinterpret_cast<const int*>(dst + p.at[2]);
+      v.cnt = reinterpret_cast<const int*>(dst + p.at[3]);
+      v.lcol = reinterpret_cast<const uint16_t*>(dst + p.at[4]);
+      std::copy(p.maxcnt.begin(), p.maxcnt.end(), d[l].pmax);
+      dst += p.bytes;
     }
-    HIP_TRY(hipStreamSynchronize(st));   // the host lists are freed on return
-    if (!ok) return fail(MG_ERR_HIP, "patch list upload failed");
     return MG_OK;
   }
   // LDS of one patch and NC columns: input, hop buffers at distance <= K - 1 and <= K - 2, three rows of zeros
@@ -2209,7 +2261,7 @@ mg_status mg_setup(const mg_hierarchy* h, const mg_params* p, const mg_options* 
   *out = nullptr;
   const ActiveCall guard;
   std::unique_ptr<EngineBase> e(make_engine(o ? o->precision : 0));
-  MG_TRY(build_plan(h, p, o, e->pl, true));
+  MG_TRY(build_plan(h, p, o, e->pl, true, [&](int l) { e->level_built(l); }));
   const size_t need = e->ws_bytes();
   if (ws && ws_bytes < need)
     return fail(MG_ERR_OOM, "workspace too small: need " + std::to_string(need) + " bytes");

@@ -13,6 +13,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <string>
 #include <thread>
@@ -456,7 +457,9 @@ void to_power_series(std::vector<double>& v, int J, int KB, int KR, int KP, int 
 
 int64_t num_params(int J, int KB, int KR, int KP) { return (int64_t)(J - 1) * (2 + (KB + 1) + (KR + 1) + (KP + 1)); }
 
-mg_status build_plan(const mg_hierarchy* h, const mg_params* p, const mg_options* o, HostPlan& pl, bool full) {
+// built(l), if given, is called when level l's operator and graph are complete (full plans)
+mg_status build_plan(const mg_hierarchy* h, const mg_params* p, const mg_options* o, HostPlan& pl, bool full,
+                     const std::function<void(int)>& built = nullptr) {
   if (!h || !p || !o) return fail(MG_ERR_INVALID_ARG, "null hierarchy, params or options");
   if (h->nlevels < 2 || !h->A || !h->P) return fail(MG_ERR_INVALID_ARG, "need nlevels >= 2 with A and P");
   if (o->nrhs < 1 || o->nrhs > kMaxB) return fail(MG_ERR_INVALID_ARG, "nrhs must be in 1..256");
@@ -534,10 +537,12 @@ mg_status build_plan(const mg_hierarchy* h, const mg_params* p, const mg_options
       pl.sym_all = false;
       pl.prow.emplace_back(h->A[l].rowptr, h->A[l].rowptr + h->A[l].nrows + 1);
       pl.pcol.emplace_back(h->A[l].col, h->A[l].col + h->A[l].nnz);
+      if (built) built(l);
     } else if (full) {
       MG_TRY(build_level(&h->A[l], h->G ? &h->G[l] : nullptr, pl.lv[l], l, p->aggregation,
                          (o->flags & MG_FLAG_BACKWARD) != 0));
       pl.sym_all = pl.sym_all && pl.lv[l].sym_A && pl.lv[l].sym_graph;
+      if (built) built(l);
     } else {
       // sizes only: widths from row counts
       HLevel& L = pl.lv[l];

@@ -15,20 +15,39 @@
 #pragma once
 #include <algorithm>
 #include <cstdint>
+#include <cstdlib>
+#include <memory>
+#include <new>
 #include <thread>
 #include <vector>
 
 namespace mgl {
+
+// Vector whose elements start uninitialised: filled by several threads, each first touching its part.
+template <class T>
+struct RawAlloc : std::allocator<T> {
+  template <class U>
+  struct rebind { using other = RawAlloc<U>; };
+  RawAlloc() = default;
+  template <class U>
+  RawAlloc(const RawAlloc<U>&) noexcept {}
+  template <class U>
+  void construct(U* p) noexcept { ::new ((void*)p) U; }
+  template <class U, class... Args>
+  void construct(U* p, Args&&... a) { ::new ((void*)p) U(std::forward<Args>(a)...); }
+};
+template <class T>
+using RawVec = std::vector<T, RawAlloc<T>>;
 
 struct TilePlan {
   int ntiles = 0;
   int KM = 0;                    // halo depth
   int wg = 0;                    // graph ELL width (a multiple of 4)
   std::vector<int> toff;         // ntiles + 1: start of each tile's node list in `node`
-  std::vector<int> node;         // global node ids, own nodes first, then by distance
+  RawVec<int> node;              // global node ids, own nodes first, then by distance
   std::vector<int> cnt;          // ntiles x (KM + 1): nodes at distance <= d from the own nodes
   std::vector<int> goff;         // ntiles + 1: start of each tile's local columns in `lcol`
-  std::vector<uint16_t> lcol;    // rows at distance <= KM - 1, wg local columns + 1 per row (0: padding)
+  RawVec<uint16_t> lcol;         // rows at distance <= KM - 1, wg local columns + 1 per row (0: padding)
   std::vector<int> maxcnt;       // KM + 1: maxima of cnt over the tiles
 };
 
@@ -60,8 +79,8 @@ namespace tiles_detail {
 // Breadth-first search from s over the nodes with placed[i] == 0, marking
 // them placed.  order receives the visit order, lstart the start of each
 // level set in it (level sets are contiguous in breadth-first order).
-// adj: row-major graph columns, wg per row.
-inline void bfs(int s, int wg, const int* adj, std::vector<char>& placed, std::vector<int>& order,
+// col: slot-major graph columns, wg slots of stride ld.
+inline void bfs(int s, int wg, int ld, const int* col, std::vector<char>& placed, std::vector<int>& order,
                 std::vector<int>& lstart) {
   order.clear();
   lstart.clear();
@@ -73,9 +92,8 @@ inline void bfs(int s, int wg, const int* adj, std::vector<char>& placed, std::v
     lstart.push_back((int)a);
     for (size_t h = a; h < e; ++h) {
       const int i = order[h];
-      const int* r = adj + (size_t)i * wg;
       for (int k = 0; k < wg; ++k) {
-        const int j = r[k];
+        const int j = col[(size_t)k * ld + i];
         if (placed[j]) continue;
         placed[j] = 1;
         order.push_back(j);
@@ -86,26 +104,16 @@ inline void bfs(int s, int wg, const int* adj, std::vector<char>& placed, std::v
   lstart.push_back((int)order.size());
 }
 
-// fn(t0, t1) over a split of [0, n) into contiguous ranges, one thread each (at most 8)
+// fn(q, t0, t1) over a split of [0, n) into contiguous ranges, one thread each (at most `most`, at most 8)
 template <class F>
-void split_run(int n, int per, F&& fn) {
+void split_run(int n, int per, int most, F&& fn) {
   const int hw = (int)std::max(1u, std::thread::hardware_concurrency());
-  const int nt = std::max(1, std::min({hw, 8, n / per + 1}));
+  const int nt = std::max(1, std::min({hw, most, 8, n / per + 1}));
   std::vector<std::thread> th;
   for (int q = 1; q < nt; ++q)
     th.emplace_back([&, q] { fn(q, (int)((long long)n * q / nt), (int)((long long)n * (q + 1) / nt)); });
   fn(0, 0, (int)((long long)n / nt));
   for (auto& x : th) x.join();
-}
-
-// row-major copy of a slot-major ELL pattern (n rows, wg slots, stride ld)
-inline std::vector<int> row_major(int n, int ld, int wg, const int* col) {
-  std::vector<int> adj((size_t)n * wg);
-  split_run(n, 16384, [&](int, int r0, int r1) {
-    for (int k = 0; k < wg; ++k)
-      for (int i = r0; i < r1; ++i) adj[(size_t)i * wg + k] = col[(size_t)k * ld + i];
-  });
-  return adj;
 }
 
 }  // namespace tiles_detail
@@ -115,13 +123,13 @@ inline std::vector<int> row_major(int n, int ld, int wg, const int* col) {
 // within a group chunk by chunk: consecutive tiles are neighbours, so a
 // tile's halo rows were mostly loaded by the tiles just before it.
 // Returns false when a tile's list would not fit 16-bit local indices.
-inline bool build_tiles(int n, int ld, int wg, const int* col, int KM, int h, int w, TilePlan& tp, int gb = 4) {
+// threads: host threads at most (8 or fewer).
+inline bool build_tiles(int n, int ld, int wg, const int* col, int KM, int h, int w, TilePlan& tp, int gb = 4,
+                        int threads = 8) {
   using tiles_detail::bfs;
   tp = TilePlan{};
   tp.KM = KM;
   tp.wg = wg;
-  const std::vector<int> adjv = tiles_detail::row_major(n, ld, wg, col);
-  const int* adj = adjv.data();
   std::vector<int> tile_of(n, -1), order, lstart;
   std::vector<char> placed(n, 0);
   int ntiles = 0, part = 0;
@@ -130,7 +138,7 @@ inline bool build_tiles(int n, int ld, int wg, const int* col, int KM, int h, in
   // one search per connected part (reachable set), from its lowest-index node
   for (int s0 = 0; s0 < n; ++s0) {
     if (placed[s0]) continue;
-    bfs(s0, wg, adj, placed, order, lstart);
+    bfs(s0, wg, ld, col, placed, order, lstart);
     const int nlev = (int)lstart.size() - 1;
     for (int b0 = 0; b0 < nlev; b0 += h) {
       const int b1 = std::min(b0 + h, nlev);
@@ -174,64 +182,80 @@ inline bool build_tiles(int n, int ld, int wg, const int* col, int KM, int h, in
   }
   tp.ntiles = ntiles;
   tp.cnt.assign((size_t)ntiles * (KM + 1), 0);
-  // halo lists, in parallel over tiles; each thread keeps its own marks
-  std::vector<std::vector<int>> lists(ntiles);
-  std::vector<std::vector<uint16_t>> lcols(ntiles);
+  // halo lists, in parallel over tiles; each thread appends to lists of its own.  A row's local columns are
+  // written as its neighbours are listed: the rows whose neighbours are listed (distance <= KM - 1) are the
+  // rows whose columns are stored.
+  struct Part {
+    RawVec<int> node;
+    RawVec<uint16_t> lcol;
+  };
+  Part parts[8];
   std::vector<char> bad(8, 0);
-  tiles_detail::split_run(ntiles, 64, [&](int tid, int t0, int t1) {
-    std::vector<int> mark(n, -1), loc(n, 0);
+  tp.toff.assign(ntiles + 1, 0);
+  tp.goff.assign(ntiles + 1, 0);
+  tiles_detail::split_run(ntiles, 64, threads, [&](int tid, int t0, int t1) {
+    Part& P = parts[tid];
+    const size_t guess = (size_t)(own_off[t1] - own_off[t0]) * 5 / 2;
+    P.node.reserve(guess);
+    P.lcol.reserve(guess * wg);
+    // a node's tile (from 1, of this thread's) and place in its list; cleared by the system, and touched
+    // only near the thread's own tiles
+    struct Place { int t, r; };
+    const std::unique_ptr<Place, decltype(&std::free)> place(static_cast<Place*>(std::calloc(n, sizeof(Place))),
+                                                             &std::free);
+    if (!place) throw std::bad_alloc();
     for (int t = t0; t < t1; ++t) {
-      std::vector<int>& L = lists[t];
-      L.assign(own.begin() + own_off[t], own.begin() + own_off[t + 1]);
-      for (int r = 0; r < (int)L.size(); ++r) { mark[L[r]] = t; loc[L[r]] = r; }
+      const size_t base = P.node.size(), lbase = P.lcol.size();
+      const int mk = t - t0 + 1;
+      P.node.insert(P.node.end(), own.begin() + own_off[t], own.begin() + own_off[t + 1]);
+      int cnt = own_off[t + 1] - own_off[t];
+      for (int r = 0; r < cnt; ++r) place.get()[P.node[base + r]] = Place{mk, r};
       int* c = &tp.cnt[(size_t)t * (KM + 1)];
-      c[0] = (int)L.size();
+      c[0] = cnt;
       int a = 0;
       for (int d = 1; d <= KM; ++d) {
-        const int e = (int)L.size();
+        const int e = cnt;
+        P.lcol.resize(lbase + (size_t)e * wg);
+        P.node.resize(base + cnt + (size_t)(e - a) * wg);
+        int* L = &P.node[base];
         for (int r = a; r < e; ++r) {
           const int g = L[r];
+          uint16_t* lc = &P.lcol[lbase + (size_t)r * wg];
           for (int k = 0; k < wg; ++k) {
-            const int j = adj[(size_t)g * wg + k];
-            if (j == g || mark[j] == t) continue;
-            mark[j] = t;
-            loc[j] = (int)L.size();
-            L.push_back(j);
+            const int j = col[(size_t)k * ld + g];
+            if (j == g) {
+              lc[k] = 0;
+              continue;
+            }
+            Place& p = place.get()[j];
+            if (p.t != mk) {
+              p = Place{mk, cnt};
+              L[cnt++] = j;
+            }
+            lc[k] = (uint16_t)(p.r + 1);
           }
         }
+        P.node.resize(base + cnt);
         a = e;
-        c[d] = (int)L.size();
+        c[d] = cnt;
       }
-      if (L.size() > 65534) { bad[tid] = 1; continue; }
-      const int rows = c[KM - 1];
-      std::vector<uint16_t>& lc = lcols[t];
-      lc.resize((size_t)rows * wg);
-      for (int r = 0; r < rows; ++r) {
-        const int g = L[r];
-        for (int k = 0; k < wg; ++k) {
-          const int j = adj[(size_t)g * wg + k];
-          lc[(size_t)r * wg + k] = (uint16_t)(j == g ? 0 : loc[j] + 1);
-        }
-      }
+      if (cnt > 65534) bad[tid] = 1;
+      tp.toff[t + 1] = cnt;
+      tp.goff[t + 1] = c[KM - 1] * wg;
     }
   });
   for (char b : bad)
     if (b) { tp = TilePlan{}; return false; }
-  tp.toff.assign(ntiles + 1, 0);
-  tp.goff.assign(ntiles + 1, 0);
   for (int t = 0; t < ntiles; ++t) {
-    tp.toff[t + 1] = tp.toff[t] + (int)lists[t].size();
-    tp.goff[t + 1] = tp.goff[t] + (int)lcols[t].size();
+    tp.toff[t + 1] += tp.toff[t];
+    tp.goff[t + 1] += tp.goff[t];
   }
   tp.node.resize(tp.toff[ntiles]);
   tp.lcol.resize(tp.goff[ntiles]);
-  tiles_detail::split_run(ntiles, 64, [&](int, int t0, int t1) {
-    for (int t = t0; t < t1; ++t) {
-      std::copy(lists[t].begin(), lists[t].end(), tp.node.begin() + tp.toff[t]);
-      std::copy(lcols[t].begin(), lcols[t].end(), tp.lcol.begin() + tp.goff[t]);
-      std::vector<int>().swap(lists[t]);
-      std::vector<uint16_t>().swap(lcols[t]);
-    }
+  tiles_detail::split_run(ntiles, 64, threads, [&](int tid, int t0, int) {   // (the ranges of the pass above)
+    Part P = std::move(parts[tid]);
+    std::copy(P.node.begin(), P.node.end(), tp.node.begin() + tp.toff[t0]);
+    std::copy(P.lcol.begin(), P.lcol.end(), tp.lcol.begin() + tp.goff[t0]);
   });
   tp.maxcnt.assign(KM + 1, 0);
   for (int t = 0; t < ntiles; ++t)
@@ -243,7 +267,7 @@ inline bool build_tiles(int n, int ld, int wg, const int* col, int KM, int h, in
 // exactly one tile, each stored local column of a row at distance d points
 // (minus one) at that neighbour, listed at distance <= d + 1, and padding
 // slots hold 0.
-inline bool check_tiles(int n, int ld, const int* col, const TilePlan& tp) {
+inline bool check_tiles(int n, int ld, const int* col, const TilePlan& tp, int threads = 8) {
   std::vector<int> owner(n, -1);
   const int KM = tp.KM;
   for (int t = 0; t < tp.ntiles; ++t) {
@@ -259,7 +283,7 @@ inline bool check_tiles(int n, int ld, const int* col, const TilePlan& tp) {
   for (int i = 0; i < n; ++i)
     if (owner[i] < 0) return false;
   std::vector<char> bad(8, 0);
-  tiles_detail::split_run(tp.ntiles, 64, [&](int tid, int t0, int t1) {
+  tiles_detail::split_run(tp.ntiles, 64, threads, [&](int tid, int t0, int t1) {
     for (int t = t0; t < t1 && !bad[tid]; ++t) {
       const int* c = &tp.cnt[(size_t)t * (KM + 1)];
       const int* L = &tp.node[tp.toff[t]];
