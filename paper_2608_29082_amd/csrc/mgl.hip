@@ -1058,7 +1058,11 @@ struct Engine final : EngineBase {
       patch_host[l] = std::move(p);
     }
     if (!bytes) return MG_OK;
-    HIP_TRY(hipMalloc(&patch_mem, bytes));
+    if (hipMalloc(&patch_mem, bytes) != hipSuccess) {   // no memory for them: the levels run by sweeps
+      (void)hipGetLastError();
+      patch_mem = nullptr;
+      return MG_OK;
+    }
     char* dst = patch_mem;
     for (int l = 0; l < J; ++l) {
       const PatchLists& p = patch_host[l];

@@ -3,7 +3,7 @@
 A request is (side, coefficient blocks, right-hand side).  The loop:
   1. setup workers (threads) build the hierarchy natively (mg_square_hierarchy;
      the GIL is released inside the library), size its device footprint
-     (mg_workspace_bytes plus the request's vectors) and wait for that much
+     (mg_workspace_bytes, the context's patch lists and the request's vectors) and wait for that much
      of the HBM budget to be free (admission by footprint), then set the
      context up (mg_setup) on their own stream;
   2. solve slots (threads, one HIP stream each) take admitted requests in
@@ -274,6 +274,10 @@ class Server:
                     hier = Bd.SquareHierarchy(req.side, req.blocks)
                     params = self._params(hier.nlevels, req.side)
                     need = self._footprint(hier, params, hier.sizes[0])
+                    # the context's patch lists, unless the whole budget does not hold them
+                    lists = patch_bytes_bound(hier.sizes, 1, self.K, self.precision)
+                    tiles = need + lists <= self.budget.total
+                    need += lists if tiles else 0
                     self.budget.acquire(need)
                     fp = need
                     with lock:
@@ -284,7 +288,7 @@ class Server:
                     with torch.cuda.stream(stream):
                         ctx = Bd.Context(None, None, params, self.K, self.K, self.K, precision=self.precision,
                                          nrhs=1, max_outer=self.max_outer, check_every=10, rtol=self.rtol,
-                                         stream=stream, device=self.device, native=hier)
+                                         stream=stream, device=self.device, native=hier, tiles=tiles)
                         f = torch.tensor(req.f, dtype=torch.float64, device=self.device)
                         work = None
                         if self.solver == "fgmres":
@@ -461,7 +465,7 @@ class BatchServer:
     draw the right-hand sides; they take requests from an Intake, one queue
     per grid side with at most 2 x capacity set-up hierarchies per side
     waiting for slots, so a side whose batch is full never holds up the other
-    sides.  Each batch's device footprint (workspace,
+    sides.  Each batch's device footprint (workspace and patch lists,
     tile lists excluded, plus f and u) is acquired from the HBM budget before its
     context is set up and released when the batch retires.  A request whose
     learned cycle diverges, or stalls (Server's test), leaves the batch and is
@@ -637,13 +641,16 @@ class BatchServer:
                     req0, _, hier0 = first[:3]
                     params = self._params(hier0.nlevels, req0.side)
                     fp = self._footprint(hier0, params)
+                    lists = patch_bytes_bound(hier0.sizes, cap, self.K, self.precision)
+                    tiles = fp + lists <= self.budget.total
+                    fp += lists if tiles else 0
                     self.budget.acquire(fp)
                     with lock:
                         self.peak_used = max(self.peak_used, self.budget.used)
                         self.batches += 1
                     ctx = Bd.Context(None, None, params, self.K, self.K, self.K, precision=self.precision, nrhs=cap,
                                      max_outer=self.cycles_per_round, check_every=2, rtol=self.rtol, stream=stream,
-                                     device=self.device, native=hier0, columns=[hier0] * cap)
+                                     device=self.device, native=hier0, columns=[hier0] * cap, tiles=tiles)
                     n = hier0.sizes[0]
                     f = torch.zeros((n, cap), dtype=torch.float64, device=self.device)
                     u = torch.zeros_like(f)
@@ -791,6 +798,22 @@ def krylov_bytes_bound(n: int, B: int, m: int) -> int:
     nB = n * B
     return (nB * ((m + 1) * 8 + m * 8 + 8) + 128 * m * 8
             + B * 8 * (1024 * (m + 2) + (m + 1) * m + 10 * (m + 2)) + (1 << 16))
+
+
+# host-built patch lists, bytes per unknown for the largest convolution order 2 .. 8 (measured on the grids'
+# operators of six neighbours: 31, 41, 52, 63, 107, 130, 220)
+_PATCH_BYTES = (36, 48, 60, 72, 128, 152, 256)
+
+
+def patch_bytes_bound(sizes, B: int, K: int, precision: str) -> int:
+    """Upper bound of the patch lists that a context on a square grid's levels
+    holds beside its workspace (mg_setup): levels of 2048 rows or more with at
+    most 2^18 entries (2^17 for K = 2), for FP64 cycles and for FP32 ones
+    whose width is no multiple of 16; 0 where there are none."""
+    if K < 2 or precision == "bf16" or (precision == "fp32" and B % 16 == 0):
+        return 0
+    top = 1 << (17 if K == 2 else 18)
+    return sum(_PATCH_BYTES[K - 2] * n + (1 << 16) for n in sizes[:-1] if n >= 2048 and n * B <= top)
 
 
 def summarize(results, wall):
