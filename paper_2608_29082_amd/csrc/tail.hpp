@@ -330,13 +330,22 @@ struct TailXfer2 {
     }
   }
 };
-// s + w t for a slot of a restriction's row (nothing for weight 0).  The per-level sweep (k_restrict)
-// rounds the product, the tail's own sum does not: `ord` as in tail_resid.
-template <class C>
-__device__ __forceinline__ C tail_rsum(C s, C w, C t, bool on, int ord) {
+// sum of w t over the first `cnt` slots of a restriction's row, from s on (weight 0: no term).  The per-level
+// sweep (k_restrict) rounds the products, the tail's own sum does not: `ord` as in tail_resid.
+template <int W, class C>
+__device__ __forceinline__ C tail_rsum(C s, const C (&w)[W], const C (&t)[W], int cnt, int ord) {
+  if (ord) {
 #pragma clang fp contract(off)
-  const C m = s + w * t;
-  return on && w != C(0) ? (ord ? m : tfma(w, t, s)) : s;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      const C m = w[k] * t[k];
+      s = k < cnt && w[k] != C(0) ? s + m : s;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < W; ++k) s = k < cnt && w[k] != C(0) ? tfma(w[k], t[k], s) : s;
+  }
+  return s;
 }
 // out[i] = (X v)_i for a transfer X to at most n_c rows; v at LDS address src.  The row's slots can be
 // loaded ahead (pre)
@@ -365,11 +374,10 @@ struct TailXfer8 {
     if (pre) {
       if constexpr (PF) {
         if ((tid & ~63) < X.n) {
-          C t[kTailW], g = C(0);
+          C t[kTailW];
 #pragma unroll
           for (int k = 0; k < kTailW; ++k) t[k] = lds_get<C>(src + j[k] * (uint32_t)sizeof(C));
-#pragma unroll
-          for (int k = 0; k < kTailW; ++k) g = tail_rsum(g, w[k], t[k], k < X.w, ord);
+          const C g = tail_rsum(C(0), w, t, X.w, ord);
           if (tid < X.n) out[tid] = g;
         }
       }
@@ -387,8 +395,7 @@ struct TailXfer8 {
           }
 #pragma unroll
           for (int k = 0; k < kTailW; ++k) t[k] = lds_get<C>(src + jj[k] * (uint32_t)sizeof(C));
-#pragma unroll
-          for (int k = 0; k < kTailW; ++k) g = tail_rsum(g, ww[k], t[k], k0 + k < X.w, ord);
+          g = tail_rsum(g, ww, t, X.w - k0, ord);
         }
         out[e] = g;
       }
@@ -550,8 +557,8 @@ __device__ __forceinline__ void tl_xfer(const Xfer<C>& X, const C* v, C* out, in
   for (int i = threadIdx.x; i < X.n; i += kTailThreads) {
     C s = C(0);
     for (int k = 0; k < X.w; ++k) {
-      const C w = X.val[(size_t)k * X.n + i];
-      s = tail_rsum(s, w, v[X.col[(size_t)k * X.n + i]], true, ord);
+      const C w[1] = {X.val[(size_t)k * X.n + i]}, t[1] = {v[X.col[(size_t)k * X.n + i]]};
+      s = tail_rsum(s, w, t, 1, ord);
     }
     out[i] = s;
   }
