@@ -1641,7 +1641,8 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_chain_tile(TileDev T, int B
         sv[e][c] = bc.ov[e][c];
         acc[e][c] = cf.c[0] * bc.xv[e][c];
         // (rows that are not the tile's own add nothing, also where x is infinite)
-        if (p0 + e * kTileNp < h.own) d = sum2_add(d, (double)bc.xv[e][c] * (double)sv[e][c]);
+        const float xo = p0 + e * kTileNp < h.own ? bc.xv[e][c] : 0.f;
+        d = sum2_add(d, (double)xo * (double)sv[e][c]);
       }
 #pragma unroll
     for (int e = 0; e < kTileRows; ++e) {
@@ -1687,7 +1688,8 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_chain_tile(TileDev T, int B
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
               acc[e][c] = hop_update(acc[e][c], ck, z[c]);
-              if (r < h.own) d = sum2_add(d, (double)z[c] * (double)sv[e][c]);
+              const float zo = r < h.own ? z[c] : 0.f;
+              d = sum2_add(d, (double)zo * (double)sv[e][c]);
             }
           }
           if (hp < K) {
