@@ -172,9 +172,10 @@ mg_status mg_workspace_bytes(const mg_hierarchy* h, const mg_params* p, const mg
  * unknown of those levels at K = 3) are allocated by the library outside
  * the workspace and freed by mg_destroy.  FP64 contexts, and FP32 contexts of
  * other widths, hold lists of patches for the levels of >= 2048 rows above the
- * coarse tail (unless MG_FLAG_NO_TILES) while rows x nrhs is at most 2^18, or
- * 2^17 where the largest convolution order is 2, or 3 * 2^19 from order 3 on
- * with edge weights.  These lists (on grids about 30 / 40 / 220 bytes per
+ * coarse tail (unless MG_FLAG_NO_TILES) where steps over patches pay: at most 28
+ * columns, rows x nrhs of at most 2^18 (2^17 where the largest convolution order
+ * is 2; 3 * 2^19 for some FP64 contexts with edge weights), and graphs with small
+ * halos.  These lists (on grids about 30 / 40 / 220 bytes per
  * unknown at order 2 / 3 / 8) are allocated and freed likewise; where there is
  * no memory for them the levels run without.  Synchronises `stream` before
  * returning. */

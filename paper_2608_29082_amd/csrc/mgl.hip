@@ -229,6 +229,8 @@ struct Engine final : EngineBase {
     int tocc[kTileMaxK + 1] = {};        // resident workgroups per compute unit
     PatchDev pd{};                  // patches of narrow batches (pd.ntiles == 0: none)
     int pmax[kTileMaxK + 1] = {};   // most nodes at distance <= k in a patch
+    double plist[kTileMaxK + 1] = {};  // nodes listed at distance <= k, over all patches
+    double pruns[kTileMaxK + 1] = {};  // and the runs of consecutive nodes they make
   };
   std::vector<DL> d;
   Lvl<double> L64{};                // level-0 operator in FP64 (outer residual)
@@ -326,6 +328,12 @@ struct Engine final : EngineBase {
   int slots_down() const { return pl.nu_post * (pl.KB + 1) + pl.KP + 1; }   // of one level, before the coarser ones
   int slots_up() const { return pl.KR + 1 + pl.nu_pre * (pl.KB + 1); }      // and after them
 
+  // whether the row sweeps of n rows on 2^lb lanes a row take four rows a lane (2048 blocks instead of 512 were
+  // 0.7 % slower on the 513 workload)
+  static bool four_rows(int n, int lb) {
+    const long rpb = 256 >> lb;
+    return (n + 4 * rpb - 1) / (4 * rpb) >= 512;
+  }
   // launch shapes of level l's row sweeps at the current cycle width
   void level_launch(int l) {
     DL& x = d[l];
@@ -333,7 +341,7 @@ struct Engine final : EngineBase {
     x.blocks = nblocks((long)n << lbs);
     const long rpb = 256 >> lbs;
     const long b4 = (n + 4 * rpb - 1) / (4 * rpb);
-    x.rows4 = b4 >= 512 ? 1 : 0;   // 2048 was 0.7 % slower on the 513 workload
+    x.rows4 = four_rows(n, lbs) ? 1 : 0;
     x.rblocks = (unsigned)(x.rows4 ? b4 : (n + rpb - 1) / rpb);
   }
   // persistent grid of level l's fused convolution of order K: the resident workgroups of
@@ -967,7 +975,7 @@ struct Engine final : EngineBase {
   }
 
   // Patches of the levels above the coarse tail that have no tiles (k_patch): for FP64 cycles and for
-  // FP32 with widths that are no multiple of kTileCols, up to patch_limit entries.  Not with BF16
+  // FP32 with widths that are no multiple of kTileCols, where they pay (patch_pays).  Not with BF16
   // intermediates, which the per-hop sweeps round.
   // The lists (36 bytes a node of a 5-point or 7-point grid with K = 3) are built on the host, a level's on
   // threads of its own from the moment its graph is known, beside the rest of the plan and the uploads.
@@ -984,13 +992,15 @@ struct Engine final : EngineBase {
     return KM <= kTileMaxK ? KM : 0;
   }
   bool patch_level(int l) const {
-    const int KM = patch_order();
-    return KM && l < pl.J - 1 && pl.lv[l].n >= kTileMinRows && (long)pl.lv[l].n * pl.B <= patch_limit(KM);
+    const int KM = patch_order(), n = pl.lv[l].n;
+    return KM && l < pl.J - 1 && n >= kTileMinRows && pl.B <= kPatchCols &&
+           (long)n * pl.B <= patch_entries(KM, n, pl.B);
   }
   struct PatchLists {
     int ntiles = 0, wg = 0;          // ntiles == 0: no patches
     bool ok = true;                  // the lists pass check_tiles
     std::vector<int> maxcnt;
+    double list[kTileMaxK + 1] = {}, runs[kTileMaxK + 1] = {};   // as DL::plist, pruns
     size_t at[5] = {}, bytes = 0;    // toff, goff, node, cnt, lcol in mem
     RawVec<char> mem;
   };
@@ -999,9 +1009,9 @@ struct Engine final : EngineBase {
     const HEll& g = H.graph_is_A ? H.off : H.graph;
     const int KM = patch_order();
     TilePlan t;
-    // 12 x 12 nodes: a cycle on 257^2 x 1 takes 6.7 / 7.0 / 7.0 ms a solve with sides of 12 / 8 / 16,
-    // one on 385^2 x 7 FP64 590 / 704 / 607 us
-    for (int side : {12, 8, 6, 4}) {
+    // 12 x 12 nodes: a solve on 257^2 x 1 takes 6.7 / 7.0 / 7.0 ms with sides of 12 / 8 / 16, a cycle on
+    // 385^2 x 7 FP64 590 / 704 / 607 us
+    for (int side : {12, 11, 10, 8, 6, 4}) {
       if (build_tiles(H.n, g.ld, g.w, g.col.data(), KM, side, side, t, MGL_TILE_GROUP, kPatchHost) &&
           t.maxcnt[KM - 1] <= kPatchThreads && t.maxcnt[KM] <= 2 * kPatchThreads &&
           patch_lds(t.maxcnt.data(), KM, 4) <= 65536)
@@ -1014,6 +1024,20 @@ struct Engine final : EngineBase {
     p.wg = t.wg;
     p.maxcnt = t.maxcnt;
     p.ok = check_tiles(H.n, g.ld, g.col.data(), t, kPatchHost);
+    for (int k = 0; k < t.ntiles; ++k) {
+      const int *c = &t.cnt[(size_t)k * (KM + 1)], *L = &t.node[t.toff[k]];
+      long runs = 1;
+      for (int d = 0, r = 1; d <= KM; ++d) {
+        for (; r < c[d]; ++r) runs += L[r] != L[r - 1] + 1;
+        p.list[d] += c[d];
+        p.runs[d] += (double)runs;
+      }
+    }
+    bool any = false;                // at the full width or a compacted one
+    for (int K : {pl.KB, pl.KR, pl.KP})
+      for (int B : {pl.B, 16})
+        any = any || (K >= 2 && B <= pl.B && patch_pays(K, H.n, B, p.list[K], p.runs[K]));
+    if (!any) return PatchLists{};
     const std::pair<const void*, size_t> part[5] = {{t.toff.data(), t.toff.size() * sizeof(int)},
                                                     {t.goff.data(), t.goff.size() * sizeof(int)},
                                                     {t.node.data(), t.node.size() * sizeof(int)},
@@ -1076,6 +1100,8 @@ struct Engine final : EngineBase {
       v.cnt = reinterpret_cast<const int*>(dst + p.at[3]);
       v.lcol = reinterpret_cast<const uint16_t*>(dst + p.at[4]);
       std::copy(p.maxcnt.begin(), p.maxcnt.end(), d[l].pmax);
+      std::copy(p.list, p.list + kTileMaxK + 1, d[l].plist);
+      std::copy(p.runs, p.runs + kTileMaxK + 1, d[l].pruns);
       dst += p.bytes;
     }
     return MG_OK;
@@ -1084,16 +1110,38 @@ struct Engine final : EngineBase {
   static size_t patch_lds(const int* most, int K, int NC) {
     return (size_t)(most[K] + most[K - 1] + (K >= 3 ? most[K - 2] : 0) + 3) * NC * sizeof(C);
   }
-  // Most entries (rows x columns) of a level whose convolutions of order K run over patches.  A patch
-  // saves launches and round trips, but reads its lists and the operator again for every four columns and
-  // computes its halo twice over, so it loses where the sweeps fill the chip.  Cycle times with the level
-  // by sweeps -> by patches, K = 3: 513^2 x 4 FP32 at 260 K entries 309 -> 295 us, 257^2 x 40 FP32 at
-  // 645 K 412 -> 452, 1025^2 at 1.05 M 375 -> 502; K = 2: 513^2 x 3 at 195 K 293 -> 282, 257^2 x 16 FP64 at
-  // 258 K 378 -> 394.  With edge weights, which a patch reads once instead of at every hop, from K = 3 on:
-  // 513^2 x 5 FP64 at 1.3 M 744 -> 575, 257^2 x 32 FP64 (K = 4) at 2.1 M 876 -> 982.
-  long patch_limit(int K) const { return K < 3 ? 1L << 17 : (wgt() ? 3L << 19 : 1L << 18); }
+  // When patches pay.  A patch saves K launches a step and their round trips, but reads its lists and the
+  // operator again for every four columns and computes its halo anew, so it wins where the sweeps are bound
+  // by launches and loses where they fill the chip or where the graph's halos are large.  What decides:
+  //  - the columns: from 32 on (where the sweeps' lanes are full) it loses 3-30 %, with 28 it is even;
+  //  - the entries (rows x columns): 2^17 for K = 2, 2^18 from K = 3 on;
+  //  - the halo: `list`, the nodes that all patches list, and `runs`, the runs of consecutive node numbers
+  //    among them (what a coalesced load covers), both at distance <= K.  Grids numbered by rows list 1.7-3.4
+  //    nodes a node in at most 0.35 K runs a node, and need no more said.  Other graphs (unstructured meshes:
+  //    2-5 nodes in 1.4-4 runs) win up to 16000 + 12000 K runs in all (48000 K with one column, whose form
+  //    is lighter), K counted up to 4, and with few enough nodes listed (three dimensions, graphs with long
+  //    edges: 5-35 nodes a node, steps up to 9 times as long as the sweeps');
+  //  - FP64 with edge weights, where the sweeps take four rows a lane and slow down: grids win throughout.
+  // Measured as a cycle with the finest level by patches against by sweeps (us saved by patches), FP32,
+  // K = 3: 129 x 129 (33000 runs with 4 columns) 37 / 28 / 20 / -13 with 1 / 4 / 12 / 28 columns; 257 x 257
+  // 35 / 26 / -7 with 1 / 4 / 8; 513 x 513 x 1 -7; an unstructured mesh of 23000 nodes 34 / 16 / -6 / -45
+  // with 1 / 4 / 8 / 20, of 92000 9 / -54 with 1 / 4; a cube of 20^3 nodes 0 / -64 / -288 with 1 / 4 / 20.
+  // 383 x 383 x 7 in FP64 with edge weights 300, 513 x 513 x 4 144.
+  static constexpr int kPatchCols = 28;
+  long patch_entries(int K, int n, int B) const {
+    if (K < 3) return 1L << 17;
+    return sizeof(C) == 8 && wgt() && B > 1 && four_rows(n, lb_shift(B)) ? 3L << 19 : 1L << 18;
+  }
+  bool patch_pays(int K, int n, int B, double list, double runs) const {
+    if (B > kPatchCols || (long)n * B > patch_entries(K, n, B)) return false;
+    const double k = std::min(K, 4);
+    if (B == 1) return list <= 2.7 * k * n && runs <= 48000 * k;
+    if (runs <= 0.35 * K * n) return true;
+    return (long)n * B <= 1L << 18 && list <= 1.1 * k * n && runs * ((B + 3) / 4) <= 16000 + 12000 * k;
+  }
   bool patched(int l, int K) const {
-    return d[l].pd.ntiles > 0 && K >= 2 && K <= d[l].pd.KM && (long)d[l].L.n * B() <= patch_limit(K);
+    const DL& D = d[l];
+    return D.pd.ntiles > 0 && K >= 2 && K <= D.pd.KM && patch_pays(K, D.L.n, B(), D.plist[K], D.pruns[K]);
   }
 
   // one launch over patches (k_patch): out = Phi(input) or (uin ? uin : 0) + scale Phi(input)

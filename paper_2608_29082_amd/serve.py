@@ -809,8 +809,8 @@ def patch_bytes_bound(sizes, B: int, K: int, precision: str) -> int:
     """Upper bound of the patch lists that a context on a square grid's levels
     holds beside its workspace (mg_setup): levels of 2048 rows or more with at
     most 2^18 entries (2^17 for K = 2), for FP64 cycles and for FP32 ones
-    whose width is no multiple of 16; 0 where there are none."""
-    if K < 2 or precision == "bf16" or (precision == "fp32" and B % 16 == 0):
+    whose width is no multiple of 16, up to 28 columns; 0 where there are none."""
+    if K < 2 or B > 28 or precision == "bf16" or (precision == "fp32" and B % 16 == 0):
         return 0
     top = 1 << (17 if K == 2 else 18)
     return sum(_PATCH_BYTES[K - 2] * n + (1 << 16) for n in sizes[:-1] if n >= 2048 and n * B <= top)
