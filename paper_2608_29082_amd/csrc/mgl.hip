@@ -714,10 +714,17 @@ struct Engine final : EngineBase {
       }
       return tail_layout(lt, t) <= (size_t)maxlds;
     };
-    // the first such level, whatever lies below it: a level without tiles (its rows too wide for their LDS)
-    // can have tiled levels below it
-    int lt = 0;
-    while (lt < J - 1 && (d[lt].td.ntiles != 0 || !fits(lt))) ++lt;
+    // A level without tiles (its rows too wide for their LDS) can have tiled levels below it.  BF16 cycles start
+    // there all the same, since the tail holds the vectors below in FP32.  Others end above the first tiled
+    // level: 5000 rows with ten neighbours each, 64 columns FP32, take 194 us a step with two levels by
+    // launches, 286 us in the tail.
+    int lt = J - 1;
+    if (std::is_same<TH, TU>::value) {
+      while (lt > 0 && d[lt - 1].td.ntiles == 0 && fits(lt - 1)) --lt;
+    } else {
+      lt = 0;
+      while (lt < J - 1 && (d[lt].td.ntiles != 0 || !fits(lt))) ++lt;
+    }
     tail_own = lt;
     if (std::is_same<TH, TU>::value && pl.KR >= 1 && lt > 1 && lt < J && d[lt - 1].td.ntiles && fits(lt - 1) &&
         rpt[lt - 1] != 0)

@@ -24,12 +24,16 @@ def _launches(family, level, prec, **kw):
     return n
 
 
-@pytest.mark.parametrize("prec", ["fp32", "bf16"])
-def test_tiled_level_below_an_untiled_one_stays_in_the_tail(prec):
-    """The tail starts at the finest level without tiles that fits its LDS and holds every level below it:
-    here the whole cycle, also the 2500 rows that have tiles (BF16 cycles keep FP32 vectors in it)."""
-    assert _launches("hop", 0, "bf16", tail=False) > 0 and _launches("conv", 1, prec, tail=False) > 0
-    assert _launches("conv", -1, prec) == 0 and _launches("resid", -1, prec) == 0
+def test_tiled_level_below_an_untiled_one_stays_in_the_tail():
+    """BF16 cycles hold FP32 vectors in the tail: it starts at the finest level without tiles that fits its LDS
+    and holds every level below it, here the whole cycle, also the 2500 rows that have tiles."""
+    assert _launches("hop", 0, "bf16", tail=False) > 0 and _launches("conv", 1, "bf16", tail=False) > 0
+    assert _launches("conv", -1, "bf16") == 0 and _launches("resid", -1, "bf16") == 0
+
+
+def test_fp32_tail_ends_below_a_wide_level():
+    """FP32 cycles, whose vectors are the same either way, run the wide level above the tiled one by launches."""
+    assert _launches("hop", 0, "fp32") > 0 and _launches("conv", 1, "fp32", tail=False) > 0
 
 
 @pytest.mark.parametrize("prec,n,width", [("fp32", 60, 6), ("fp32", 900, 6), ("fp32", 1300, 10), ("fp32", 4000, 8),
