@@ -1223,7 +1223,14 @@ struct Engine final : EngineBase {
   // (the restriction then scales after its sum).
   bool in_tail(int l, int uz, bool ck) const {
     if (tail_lt < 0 || l < tail_lt || l >= pl.J - 1) return false;
-    return (uz && !ck) || (std::is_same<TH, TU>::value && pl.KR >= 1);
+    if (uz && !ck) return true;
+    if (!std::is_same<TH, TU>::value || pl.KR < 1) return false;
+    // The tail's own sums are fixed by the cycle from zero.  The others carry the same bits either way, and
+    // where the first level runs by the generic sweeps (no register variant), one workgroup a column is slower
+    // than launches from 2000 rows on, up to 64 columns at the least: cycles from a nonzero iterate with that
+    // level in the tail -> by launches, ten neighbours a row, 5000 rows 270 -> 150 us with one column, 287 -> 184
+    // with 64, 315 -> 331 with 250; 2100 rows 153 -> 137, 157 -> 147, 176 -> 248; 1300 rows 110 -> 124, 113 -> 125.
+    return tails[l - tail_lt].lv[0].rpt != 0 || pl.lv[l].n < 2000 || B() > 64;
   }
   // e = LMG(A_l, f, e) (uz: e is zero on entry; fmg: e = FMG(f)) for levels l .. J-1 in one launch;
   // with ck, the levels below l are recorded there

@@ -36,6 +36,40 @@ def test_fp32_tail_ends_below_a_wide_level():
     assert _launches("hop", 0, "fp32") > 0 and _launches("conv", 1, "fp32", tail=False) > 0
 
 
+@pytest.mark.parametrize("n,width,B,inside", [(5000, 10, 5, False), (5000, 10, 64, False), (2100, 10, 3, False),
+                                              (1300, 10, 3, True), (4000, 8, 3, True), (5000, 10, 70, True)])
+def test_nonzero_iterate_over_a_level_of_generic_sweeps(n, width, B, inside):
+    """Cycles from a nonzero iterate and those that record a checkpoint run a first level of the tail that has no
+    register variant by launches where these are faster; a step that records carries the sweeps' bits."""
+    import numpy as np
+    import torch
+    from oracle import lmg as O
+    from paper_2608_29082_amd import binding as Bd
+    from tests.gpu_util import elem_rel, to_np
+    from tests.test_gpu_tail import TOL
+    A, P = _hierarchy(n, width, n)
+    J, K = len(A), 3
+    flat = C.random_params(J, K, K, K, seed=n, spread=0.1)
+    g = C.rng(11, 9, n)
+    f, u = (g.standard_normal((n, B)).astype(np.float32).astype(np.float64) for _ in range(2))
+    fd, ud = to_dev(f, torch.float64), to_dev(u, torch.float64)
+    steps, launches = [], []
+    for tail in (True, False):
+        ctx = Bd.Context(A, P, flat, K, K, K, precision="fp32", nrhs=B, tail=tail, tiles=False, backward=True)
+        v = ud.float()
+        for call in (lambda: ctx.refine_step(fd, torch.zeros_like(fd)), lambda: ctx.vcycle(fd.float(), v),
+                     lambda: steps.append(to_np(ctx.refine_step(fd, ud, ckpt=ctx.new_ckpt())))):
+            ctx.timing_start("hop", 0)
+            call()
+            launches.append(ctx.timing_read()[0])
+            ctx.timing_start(None)
+        want = O.lmg(O.make_levels(A, P), O.unpack(flat, J, K, K, K), 0, f, u)
+        assert elem_rel(to_np(v), want) <= TOL["fp32"]
+        ctx.close()
+    assert launches[0] == 0 and [k == 0 for k in launches[1:3]] == [inside, inside] and min(launches[3:]) > 0
+    assert np.array_equal(*steps)
+
+
 @pytest.mark.parametrize("prec,n,width", [("fp32", 60, 6), ("fp32", 900, 6), ("fp32", 1300, 10), ("fp32", 4000, 8),
                                           ("fp64", 900, 6), ("fp64", 2100, 4)])
 def test_restriction_in_the_tail_rounds_as_the_sweeps(prec, n, width):
