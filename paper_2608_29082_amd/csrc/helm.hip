@@ -634,11 +634,12 @@ __global__ __launch_bounds__(MODE == 1 ? kGT : kGTH) void k_hz_gmres(CEll<T> A, 
 }
 
 // ------------------------------------------------------------------ GMRES smoothing step, rows in registers
-// The same step for levels of at most 1536 rows (4608 in FP32, gmres_fn) with each
-// work-item's rows (1, 3 or 9 of them, row r of work-item t being t + r * 512) in
-// registers: A's rows (not with 9), r, d0, u and the basis vectors.  Only what neighbours read is in LDS: the vector a
-// sparse product gathers, in two buffers used in turn, so a product costs one
-// barrier and the Gram-Schmidt sweeps none.
+// The same step for levels of at most 1536 rows (in FP32 also of 3073 .. 4608,
+// gmres_fn) with each work-item's rows (1, 3 or 9 of them, row r of work-item t
+// being t + r * 512) in registers: A's rows (not with 9), r, d0, u and the basis
+// vectors.  Only what neighbours read is in LDS: the vector a sparse product
+// gathers, in two buffers used in turn, so a product costs one barrier and the
+// Gram-Schmidt sweeps none.
 //
 // What bounds it: one workgroup per column walks 6 dependent products and 2 v
 // + 1 reductions, so the cost is latency.  The reductions dominated the sweep
@@ -647,7 +648,11 @@ __global__ __launch_bounds__(MODE == 1 ? kGT : kGTH) void k_hz_gmres(CEll<T> A, 
 // the values a lane carries (row operations and the gfx950 row swaps, no LDS),
 // one barrier per reduction (two buffers in turn), and every wavefront sums
 // the waves' totals by itself into scalars.  512 work-items, so that a
-// work-item has 256 registers.
+// work-item has 256 registers.  One row takes 142-150 of them and three rows
+// 190-240 (eight slots in FP64: all, with 10 spilled); the nine-row form spills
+// 155 (296 bytes of scratch a lane), and still reads less than the sweep form.
+// Us a launch, sweep form -> this one: 65 -> 24 on 33 x 33 x 16 in FP32, 145 ->
+// 91 on 65 x 65 x 16.
 constexpr int kGR = 512;
 constexpr int kGRv = 4;          // GMRES steps of this form (at most)
 constexpr int kGRw = 8;          // slots per row (at most)
@@ -1456,9 +1461,12 @@ struct HzEngine final : mgh_ctx {
   using GmresFn = void (*)(CEll<T>, GEll, const T*, int, const cx<T>*, cx<T>*, T, T, WK<T>, int, int);
   // The GMRES smoothing step with rows in registers for a level of n rows of w slots (null: the sweep
   // form, for more than kGRv steps, wider rows, or more than three rows per work-item).  Nine rows
-  // do not leave registers for A's, which each product reads again from the L2: FP32 65 x 65 levels
-  // (x 16) go from 145 to 90 us, FP64 ones from 208 to 225, so FP32 only, and only where at least two
-  // thirds of the nine are rows
+  // do not leave registers for A's, which each product reads again from the L2: FP64 65 x 65 x 16 goes
+  // from 208 to 225 us a step, so FP32 only, and only where at least two thirds of the nine are rows.  A
+  // two-level cycle with two such steps, sweep form -> nine rows: 282 -> 200 us on 57 x 57 x 16, 331 -> 227
+  // on 65 x 65 x 16, 571 -> 486 and 742 -> 618 with 256 columns, 129 -> 121 on 57 x 57 x 16 with one GMRES
+  // step and K = 0.  Between 1537 and 3072 rows there is no register form (45 x 45 x 16: 192 us, where
+  // 39 x 39 x 16 takes 73): none of four to six rows was built.
   static GmresFn gmres_fn(int n, int w, int v) {
     if (v > kGRv || w > kGRw || w < 1) return nullptr;
     if constexpr (std::is_same<T, float>::value)

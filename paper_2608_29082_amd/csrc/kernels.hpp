@@ -1554,7 +1554,7 @@ __global__ __launch_bounds__(256) void k_hopT(Lvl<C> L, int B, int lbs, const TZ
 // the row scale applied as rows enter LDS (a transposed hop sums r_j z_j), the sum acc of the own
 // nodes in registers and their dot products with s, slot k of this block at
 // part[k * gridDim.x + blockIdx.x].  What bounds it is what bounds k_conv_tile (the LDS gathers; four
-// wavefronts a SIMD hide the prefetch): 14.5 us with K = 3, the mean over levels of 255 x 255 and
+// wavefronts a SIMD hide the prefetch): 14.9 us with K = 3, the mean over levels of 255 x 255 and
 // 127 x 127 x 32; the four hops' sweeps and the scaling's took 62 on the finer of them alone.
 template <bool WG, class TS>
 __global__ __launch_bounds__(kTileThreads, 4) void k_chain_tile(TileDev T, int B, int K, TileCoef cf,
@@ -1779,7 +1779,7 @@ static __global__ __launch_bounds__(256) void k_dots_final(const Sum2* __restric
 }
 
 // Parameter gradients from the dot products: one work-item per parameter, each adding the slots that
-// belong to it in slot order (12 us at 150 slots, 26 at 290; one work-item adding all of the 150 took 61).
+// belong to it in slot order (12 us at 150 slots, 21-26 at 290; one work-item adding all of the 150 took 61).
 // desc[s] = {kind (0 smoother, 1 restriction, 2 prolongation), level, k}.
 // Smoother dot e = <(M^T)^k g, s> with s = D^{-1}(f - A u):
 //   dc_k += eta theta e,  deta += theta c_k e,  dtheta += eta c_k e.

@@ -686,9 +686,12 @@ struct Engine final : EngineBase {
   //    largest) fit the workgroup's LDS; with 65 x 65 unknowns and one column the whole cycle is
   //    then one launch.
   //  - Where the cycle's vectors are not rounded to BF16, one tiled level of at most 4096 rows above
-  //    them joins too, unless it is the finest: its 12 launches (two smoothing steps on each side, the
-  //    transfers) take ~75 us whatever the batch, the tail's visit of 63 x 63 rows 15-20 us.  It sums its
-  //    residuals in the order of the per-level sweeps (TailArgs::nord), so no bit of the cycle changes.
+  //    them joins too, unless it is the finest: one workgroup a column visits 63 x 63 rows sooner than 12
+  //    launches run on them (two smoothing steps on each side, the transfers), whatever the batch.  A cycle
+  //    on 129 x 129 with the level by launches -> in the tail: 133 -> 111 us with 16 columns, 166 -> 142
+  //    with 64, 209 -> 180 with 128, 289 -> 242 with 256; V(1,1) with K = 2 and edge weights, the least
+  //    gain, 190 -> 178 with 256.  It sums its residuals and restrictions as the per-level sweeps do
+  //    (TailArgs::nord), so no bit of the cycle changes.
   mg_status setup_tail() {
     tail_lt = -1;
     tails.clear();
@@ -758,7 +761,6 @@ struct Engine final : EngineBase {
       t.nu_pre = pl.nu_pre; t.nu_post = pl.nu_post; t.per = per();
       t.prm = dprm + (size_t)lt * per();
       t.Ainv = Ainv;
-      t.lt = lt;
       t.nord = std::max(0, tail_own - lt);
       tails.push_back(t);
       tail_bytes.push_back(bytes);
@@ -811,7 +813,6 @@ struct Engine final : EngineBase {
     a.T.nu_pre = pl.nu_pre; a.T.nu_post = pl.nu_post; a.T.per = per();
     a.T.prm = dprm + (size_t)lt * per();
     a.T.Ainv = Ainv;
-    a.T.lt = lt;
     const int nl = J - lt;
     for (int q = 0; q < nl; ++q) {
       const DL& x = d[lt + q];
@@ -1170,7 +1171,10 @@ struct Engine final : EngineBase {
         const double bytes = nB(l) * sizeof(C) * (FRONT == 1 ? 2 : 1) + nB(l) * sizeof(C) * (mode && uin ? 2 : 1) +
                              (FRONT == 1 ? bytes_A(l) : (FRONT == 2 ? bytes_X(D.P) : 0.0)) +
                              (double)D.L.wg * D.L.n * (4 + (wgt() ? sizeof(C) : 0)) + (double)D.L.n * sizeof(C);
-#define MGL_PATCH(W_)                                                                                               TIMED(MG_KF_CONV, bytes,                                                                                                WG_SPLIT(hipLaunchKernelGGL((k_patch<FRONT, W_, NC, WGv, C>), dim3(grid), dim3(nt), lds, st, D.pd, D.L, D.P,                                     B(), K, cf, x, u, xsc, uin, out, mode, (C)scale, y0, y1)))
+#define MGL_PATCH(W_)                                                                                                \
+  TIMED(MG_KF_CONV, bytes,                                                                                           \
+        WG_SPLIT(hipLaunchKernelGGL((k_patch<FRONT, W_, NC, WGv, C>), dim3(grid), dim3(nt), lds, st, D.pd, D.L, D.P, \
+                                    B(), K, cf, x, u, xsc, uin, out, mode, (C)scale, y0, y1)))
         if (D.pd.wg <= 8) MGL_PATCH(8);
         else MGL_PATCH(0);
 #undef MGL_PATCH
@@ -2207,8 +2211,8 @@ struct Engine final : EngineBase {
     if (!gp) return MG_OK;
     hipLaunchKernelGGL(k_dots_final, dim3(nslots), dim3(256), 0, st, dpart, doff, dcnt, nslots, dots);
     LAUNCH_OK();
-    hipLaunchKernelGGL(k_grad_combine, dim3(nblocks((long)pl.params.size())), dim3(256), 0, st, dots, ddesc, nslots, dprm, per(), pl.KB, pl.KR, gp,
-                       (int)pl.params.size());
+    hipLaunchKernelGGL(k_grad_combine, dim3(nblocks((long)pl.params.size())), dim3(256), 0, st, dots, ddesc, nslots,
+                       dprm, per(), pl.KB, pl.KR, gp, (int)pl.params.size());
     LAUNCH_OK();
     if (pl.basis == MG_BASIS_CHEBYSHEV) {
       hipLaunchKernelGGL(k_cheb_grad, dim3(1), dim3(64), 0, st, gp, pl.J - 1, per(), pl.KB, pl.KR, pl.KP,

@@ -11,12 +11,17 @@
 // into registers: 1 .. 4 rows per work-item (row r of work-item t is
 // t + r * 1024) with the operator's values, the row scales and the neighbours'
 // LDS addresses.  The rows' own f, u and convolution input stay in registers
-// too, so a sweep is W LDS reads per row, the sums and one LDS write.  Slot counts are compile-time (W = 4, 6 or 8, the
-// widest row of the level rounded up), so a sweep's reads are all in flight
-// before the first is used; a slot that a row does not have reads the zero
-// kept behind each vector.  Levels of at most 64 rows run on the first
-// wavefront without workgroup barriers.  The parameters and a small coarsest
-// inverse are copied to LDS once per launch.
+// too, so a sweep is W LDS reads per row, the sums and one LDS write.  Slot
+// counts are compile-time (W = 4, 6 or 8, the widest row of the level rounded
+// up), so a sweep's reads are all in flight before the first is used; a slot
+// that a row does not have reads the zero kept behind each vector.  Levels of
+// at most 64 rows run on the first wavefront without workgroup barriers.  The
+// parameters and a small coarsest inverse are copied to LDS once per launch.
+//
+// Measured (us a launch): 33 x 33 x 1 in FP64 26 for a whole cycle (78 with
+// rows read in every sweep), 65 x 65 x 1 in FP32 52, levels of 63 x 63 and
+// below with 64 columns 71, with 32 columns' own operators 113 (a value of one
+// column is 4 bytes in every 128 read).
 //
 // Levels that do not fit this form (rows of more than 8 neighbours, or more
 // rows than the register variants hold) run the generic sweeps tl_*, which
@@ -51,7 +56,6 @@ struct TailArgs {
   const double* prm;        // flat parameters, row `per` per level, first tail level first
   const double* Ainv;       // coarsest inverse (row-major)
   int nJ;
-  int lt;                   // global index of the first tail level
   int nord;                 // the first nord levels sum a residual in the order of the per-level sweeps
   C* ckf[kTailMaxLevels];   // checkpoint of the levels below the first (null: not recorded)
   C* cku[kTailMaxLevels];
@@ -621,11 +625,14 @@ __device__ __forceinline__ void tail_visit_generic(const TailArgs<C>& T, C* sm, 
   }
 }
 
-// Register variants by element size, the widest that stay within the 128
-// registers of a 1024-work-item workgroup: FP32 holds up to four rows of eight
-// slots (4096 rows; the edge weights of more than two rows are read again in
-// each sweep), FP64 the values of up to two rows (one with edge weights) and the
-// addresses of three.
+// Register variants by element size, for the 128 registers of a 1024-work-item
+// workgroup: FP32 holds up to four rows of eight slots (4096 rows; the edge
+// weights of more than two rows are read again in each sweep), FP64 the values
+// of up to two rows (one with edge weights) and the addresses of three.  One
+// kernel holds them all, and its register allocation is that of the whole: the
+// compiler reports 108 spilled vector registers in FP32 (122 with edge weights)
+// and 32 in FP64, where a kernel of the four-row FP32 variant alone spills 18,
+// of the three-row one at most 2 and of the smaller ones none.
 template <class C> constexpr int tail_max_rpt() { return sizeof(C) == 4 ? 4 : 3; }
 
 template <bool WG, class C>
@@ -787,12 +794,14 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<C> args, int B, 
 // per level the forward recomputation, the transposed post-smoothing and
 // prolongation (phase 0), then, after the coarser levels, the transposed
 // restriction and pre-smoothing (phase 1), in the order of operations of the
-// per-level sweeps (same bits).  What bounds it is what bounds k_tail: ~45 dependent sweeps a
-// level, where the per-level form paid ~75 launches.  A transposed hop
-// z = G^T y is the neighbour sum of the row-scaled vector, so it reads LDS like a
-// forward hop.  What a level keeps between its phases (S_j, the residual, P e, g
-// and gf) is private to a row and lives in the level's workspace vectors,
-// stored column by column.
+// per-level sweeps (same bits).  What bounds it is what bounds k_tail: ~45
+// dependent sweeps a level, where the per-level form paid ~75 launches.  A
+// transposed hop z = G^T y is the neighbour sum of the row-scaled vector, so it
+// reads LDS like a forward hop.  Its merged variants spill too: 206 vector
+// registers in FP32 (419 with edge weights; the four-row ones alone 13 to 48),
+// none in FP64 (37); 164 us a launch from 63 x 63 x 32 down.  What a level keeps
+// between its phases (S_j, the residual, P e, g and gf) is private to a row and
+// lives in the level's workspace vectors, stored column by column.
 template <class C>
 struct TailBwdLevel {
   Xfer<C> PT, RT;           // n_{l+1} x n_l and n_l x n_{l+1}
@@ -991,7 +1000,7 @@ __device__ __forceinline__ void tail_bwd_visit(const TailBwdArgs<C>& A, C* sm, u
     tail_sync<WAVE>();
     TailXfer8<false, C> R;
     R.load(tb.PT, Rows::nt, false);
-    R.apply(tb.PT, Rows::nt, wk + out, sm + T.lv[q + 1].off_u, 0);   // (by k_prolong level by level)
+    R.apply(tb.PT, Rows::nt, wk + out, sm + T.lv[q + 1].off_u, 0);   // (k_prolong fuses its products)
   } else {
     TailXfer2<RPT, C> P;
     if (M.act) P.load(tb.RT, M.ic);
