@@ -17,8 +17,8 @@
 #include <future>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <type_traits>
 #include <vector>
@@ -1059,6 +1059,13 @@ struct Engine final : EngineBase {
     for (int k = 0; k < 5; ++k) std::memcpy(p.mem.data() + p.at[k], part[k].first, part[k].second);
     return p;
   }
+  PatchLists try_patches(int l) const {
+    try {
+      return plan_patches(l);
+    } catch (const std::bad_alloc&) {   // no host memory for them: the level runs by sweeps
+      return PatchLists{};
+    }
+  }
   std::vector<std::future<PatchLists>> patch_jobs;  // per level (waits for its threads when it goes)
   std::vector<PatchLists> patch_host;               // the lists until their uploads have ended
   void level_built(int l) override {
@@ -1069,8 +1076,8 @@ struct Engine final : EngineBase {
     const bool tail = !(pl.flags & MG_FLAG_NO_TAIL) && pl.lv[l].n <= tail_max_rpt<C>() * kTailThreads;
     if (tiles || tail || !patch_level(l)) return;
     try {
-      patch_jobs[l] = std::async(std::launch::async, [this, l] { return plan_patches(l); });
-    } catch (const std::system_error&) {   // no thread to be had: likewise
+      patch_jobs[l] = std::async(std::launch::async, [this, l] { return try_patches(l); });
+    } catch (...) {   // no thread to be had: likewise
     }
   }
   mg_status setup_patches(hipStream_t st) {
@@ -1084,7 +1091,7 @@ struct Engine final : EngineBase {
       PatchLists p;
       if (job) p = patch_jobs[l].get();
       if (l >= std::min(lt, J - 1) || d[l].td.ntiles || !patch_level(l)) continue;
-      if (!job) p = plan_patches(l);
+      if (!job) p = try_patches(l);
       if (!p.ok) return fail(MG_ERR_STATE, "patch lists of level " + std::to_string(l) + " are inconsistent");
       bytes += p.bytes;
       patch_host[l] = std::move(p);

@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstdlib>
+#include <exception>
 #include <memory>
 #include <new>
 #include <thread>
@@ -104,16 +105,32 @@ inline void bfs(int s, int wg, int ld, const int* col, std::vector<char>& placed
   lstart.push_back((int)order.size());
 }
 
-// fn(q, t0, t1) over a split of [0, n) into contiguous ranges, one thread each (at most `most`, at most 8)
+// fn(q, t0, t1) over a split of [0, n) into contiguous ranges, one thread each (at most `most`, at most 8).
+// Ranges that get no thread run on the caller's; an exception of any range is thrown again here.
 template <class F>
 void split_run(int n, int per, int most, F&& fn) {
   const int hw = (int)std::max(1u, std::thread::hardware_concurrency());
   const int nt = std::max(1, std::min({hw, most, 8, n / per + 1}));
+  std::exception_ptr err[8];
+  auto range = [&](int q) {
+    try {
+      fn(q, (int)((long long)n * q / nt), (int)((long long)n * (q + 1) / nt));
+    } catch (...) {
+      err[q] = std::current_exception();
+    }
+  };
   std::vector<std::thread> th;
-  for (int q = 1; q < nt; ++q)
-    th.emplace_back([&, q] { fn(q, (int)((long long)n * q / nt), (int)((long long)n * (q + 1) / nt)); });
-  fn(0, 0, (int)((long long)n / nt));
+  th.reserve(nt);
+  int q = 1;
+  try {
+    for (; q < nt; ++q) th.emplace_back(range, q);
+  } catch (...) {   // no thread to be had
+  }
+  range(0);
+  for (; q < nt; ++q) range(q);
   for (auto& x : th) x.join();
+  for (const std::exception_ptr& e : err)
+    if (e) std::rethrow_exception(e);
 }
 
 }  // namespace tiles_detail
